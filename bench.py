@@ -63,7 +63,8 @@ def kernel_source_hash(proc):
     import hashlib
     from paper_2106_12631_amd import build as _build
     csrc = os.path.join(ROOT, 'paper_2106_12631_amd', 'csrc')
-    shared = ['colour_mfma.h', 'common.h', 'helas.h', 'internal.h', 'sigmakin_impl.h']
+    shared = ['colour_mfma.h', 'common.h', 'helas.h', 'internal.h', 'shared_currents.h',
+              'sigmakin_impl.h']
     gen = os.path.join(csrc, 'generated')
     units = sorted(os.path.join('generated', n) for n in os.listdir(gen)
                    if n.startswith(f'sigmakin_{proc}_') and n.endswith('.hip'))

@@ -1,0 +1,652 @@
+// g g -> t t~ + gluons with every current shared by the helicities that do
+// not distinguish it.
+//
+// A current of k external legs has 2^k helicity versions, not 2^npar: the
+// kernels built on this header compute each version once per event and
+// assemble the colour flows of a helicity from them, instead of running all
+// the currents of all the diagrams for every helicity.  The diagrams of a
+// colour flow are summed inside the currents (Berends-Giele recursion), with
+// the Feynman rules, couplings and propagators of helas.h:
+//
+//   J(a)       polarisation vector of gluon a
+//   J(w)       = g/K^2 [ -sum_{w = xy} L(J(x), J(y)) + g sum_{w = xyz} Q(J(x), J(y), J(z)) ]
+//   L(x, y)    = x (-(2 kx + ky).y) + (x.y) (kx - ky) + y ((kx + 2 ky).x)
+//   Q(x, y, z) = 2 y (x.z) - x (y.z) - z (x.y)
+//   U(w)       = -g sum_{w = xy} U(x) J-slash(y) (q-slash + m) / D      t line from the t end
+//   W(w)       = -g sum_{w = xy} (q-slash + m) / D J-slash(x) W(y)      and from the t~ end
+//
+// J(w) with w = (word of gluons) is the coefficient of the string of SU(3)
+// generators T^w in the current.  J(ab) = -J(ba); the six orderings of three
+// gluons have one value per middle gluon, and the three sum to zero; a
+// four-gluon current changes sign under reversal.
+//
+// Row spinors f of the t side are kept as columns (f1, -f0, f3, -f2), on
+// which f V-slash acts as V-slash on a column, so that both ends of the line
+// run through the same code.
+#pragma once
+#include "common.h"
+
+namespace mg {
+
+typedef double d2 __attribute__((ext_vector_type(2)));  // one complex in LDS: 16-byte accesses
+typedef cx<double> c64;
+
+// four components of version v of an object whose components are `n` apart
+// (component-major: the versions that the lanes of a wave read lie next to
+// each other, so a read is free of bank conflicts)
+__device__ __forceinline__ void lds_get(const d2* p, int n, c64 (&w)[4]) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const d2 t = p[k * n];
+    w[k] = c64{t.x, t.y};
+  }
+}
+__device__ __forceinline__ void lds_put(d2* p, int n, const c64 (&w)[4]) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) p[k * n] = d2{w[k].r, w[k].i};
+}
+// polarisation vector: no time component, real z component (ext_vector)
+__device__ __forceinline__ void lds_get_eps(const d2* p, c64 (&w)[4]) {
+  const d2 a = p[8], b = p[16];
+  w[0] = c64{0.0, 0.0};
+  w[1] = c64{a.x, a.y};
+  w[2] = c64{b.x, b.y};
+  w[3] = c64{p[24].x, 0.0};
+}
+__device__ __forceinline__ c64 lds_scalar(const d2* p) {
+  const d2 t = *p;
+  return c64{t.x, t.y};
+}
+__device__ __forceinline__ void lds_get_real(const d2* p, double (&k)[4]) {
+  const d2 a = p[0], b = p[1];
+  k[0] = a.x;
+  k[1] = a.y;
+  k[2] = b.x;
+  k[3] = b.y;
+}
+
+// acc + a.b (Minkowski)
+__device__ __forceinline__ c64 mdot_add(const c64 (&a)[4], const c64 (&b)[4], c64 acc) {
+  return cmsub(a[3], b[3], cmsub(a[2], b[2], cmsub(a[1], b[1], cmadd(a[0], b[0], acc))));
+}
+__device__ __forceinline__ c64 mdot0(const c64 (&a)[4], const c64 (&b)[4]) {
+  return cmsub(a[3], b[3], cmsub(a[2], b[2], cmsub(a[1], b[1], a[0] * b[0])));
+}
+// acc + (row spinor kept as column u) times column w
+__device__ __forceinline__ c64 sdot_add(const c64 (&u)[4], const c64 (&w)[4], c64 acc) {
+  return cmsub(u[3], w[2], cmadd(u[2], w[3], cmsub(u[1], w[0], cmadd(u[0], w[1], acc))));
+}
+// F gamma^mu G for the row spinor F kept as column u
+__device__ __forceinline__ void bilinear(const c64 (&u)[4], const c64 (&G)[4], c64 (&J)[4]) {
+  const c64 F[4] = {-u[1], u[0], -u[3], u[2]};
+  ffv_bilinear_v<double>(F, G, J);
+}
+// V-slash acting on a column
+__device__ __forceinline__ void slash_col(const c64 (&V)[4], const c64 (&G)[4], c64 (&f)[4]) {
+  blk<double> s, sb;
+  slash_blocks(V, s, sb);
+  mcol(s, G[2], G[3], f[0], f[1]);
+  mcol(sb, G[0], G[1], f[2], f[3]);
+}
+__device__ __forceinline__ void slash_col_add(const c64 (&V)[4], const c64 (&G)[4], c64 (&f)[4]) {
+  blk<double> s, sb;
+  slash_blocks(V, s, sb);
+  f[0] = cmadd(s.a, G[2], cmadd(s.b, G[3], f[0]));
+  f[1] = cmadd(s.c, G[2], cmadd(s.d, G[3], f[1]));
+  f[2] = cmadd(sb.a, G[0], cmadd(sb.b, G[1], f[2]));
+  f[3] = cmadd(sb.c, G[0], cmadd(sb.d, G[1], f[3]));
+}
+// d (q-slash + m) f
+__device__ __forceinline__ void propagate(const double (&q)[4], double m, c64 d, const c64 (&f)[4],
+                                          c64 (&out)[4]) {
+  c64 y0, y1, y2, y3;
+  sK_col(q, f[2], f[3], y0, y1);
+  sbK_col(q, f[0], f[1], y2, y3);
+  out[0] = d * rmadd(m, f[0], y0);
+  out[1] = d * rmadd(m, f[1], y1);
+  out[2] = d * rmadd(m, f[2], y2);
+  out[3] = d * rmadd(m, f[3], y3);
+}
+// L(x, y) of the three-gluon vertex
+__device__ __forceinline__ void three_gluon(const c64 (&x)[4], const double (&kx)[4],
+                                            const c64 (&y)[4], const double (&ky)[4],
+                                            c64 (&out)[4]) {
+  double qx[4], qy[4], dk[4];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    qx[m] = -(2.0 * kx[m] + ky[m]);
+    qy[m] = kx[m] + 2.0 * ky[m];
+    dk[m] = kx[m] - ky[m];
+  }
+  const c64 cx_ = mdot(qx, y), cy_ = mdot(qy, x), xy = mdot0(x, y);
+#pragma unroll
+  for (int m = 0; m < 4; ++m) out[m] = rmadd(dk[m], xy, cmadd(y[m], cy_, x[m] * cx_));
+}
+
+// Spinors of the t (mapped to a column) and the t~: ubar(p, lam) of helas.h
+// mapped, or v(p, lam), one branch-free body for the lanes of both
+__device__ __forceinline__ void top_spinor(const double (&p)[4], double m, int lam, bool anti,
+                                           c64 (&w)[4]) {
+  double wm, wp, c0r, c0i, c1r, c1i;
+  omegas(p, m, lam, wm, wp);
+  helicity_chi(p, anti ? -lam : lam, c0r, c0i, c1r, c1i);
+  const c64 a0{wp * c0r, wp * c0i}, a1{wp * c1r, wp * c1i};
+  const c64 b0{wm * c0r, wm * c0i}, b1{wm * c1r, wm * c1i};
+  if (anti) {  // (wp chi, -wm chi)
+    w[0] = a0;
+    w[1] = a1;
+    w[2] = -b0;
+    w[3] = -b1;
+  } else {     // row (wp chi^+, wm chi^+) as the column (f1, -f0, f3, -f2)
+    w[0] = conj(a1);
+    w[1] = -conj(a0);
+    w[2] = conj(b1);
+    w[3] = -conj(b0);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// g g -> t t~ g g: one event per wave
+// ---------------------------------------------------------------------------
+// Gluons 0..3 = legs 0, 1, 4, 5; colour flows = orderings of the gluons in
+// lexicographic order.  With the quark line cut between its second and third
+// gluon, the flow (a b c d) is
+//   A = g [ U(ab).(c-slash W(d) + J-slash(cd) v) + J(bc).G(a, d)
+//         + J(bcd).Y(a) + J(abc).Z(d) + g/K^2 (-P(ab|cd) + g quartic) ]
+//   G(a, d) = U(a) gamma W(d)
+//   Y(a) = U(a) gamma v + (g/K^2) X(a),  Z(d) = u gamma W(d) - (g/K^2) X(d)
+//   B = u gamma v,  X(a) = L(a, B),  P(ab|cd) = L(J(ab), J(cd)).B
+// (K the momentum of all four gluons; the three-gluon vertex is
+// antisymmetric in its three legs, so L(J(abc), d).B = J(abc).L(d, B)).
+//
+// The currents are built by the lanes side by side (a lane per current and
+// helicity version) and handed on through LDS; then lane h assembles the 24
+// flows of helicity h.  Bound: FP64 VALU (busy 80 % of the time, two waves per
+// SIMD of 229 registers and 18 KB of LDS each): 4.0e3 VALU instructions per
+// event in place of 18.3e3 with one full amplitude per lane; 2^19 events in
+// 4.4 ms, 119 M events/s (19.3 ms, 27.2 M with one full amplitude per lane).
+namespace ggttgg_shared {
+
+// LDS in units of one complex (16 bytes); versions are bit fields of the
+// helicities in the order named, lowest bit first
+constexpr int EPS = 0;             // [4][8]   2 g + h
+constexpr int QV = EPS + 32;       // [4][4]   2 side + h (side 0: t, 1: t~)
+constexpr int KV = QV + 16;        // [32][2]  momenta, see momentum slots below
+constexpr int PR = KV + 64;        // [32]     propagator factors of the slots
+constexpr int J2 = PR + 32;        // [4][24]  pair * 4 + (a, b)
+constexpr int U1 = J2 + 96;        // [4][32]  side * 16 + g * 4 + (quark, g)
+constexpr int BB = U1 + 128;       // [4][4]   (t, t~)
+constexpr int R = BB + 16;         // reused by the stages
+//   stage 1
+constexpr int NN = R;              // [4][48]  pairing * 16 + (0, 1, 2, 3)
+constexpr int JB = NN + 192;       // [96]     J(ab).B   pair * 16 + (t, t~, a, b)
+constexpr int CB = JB + 96;        // [32]     c.B       g * 8 + (t, t~, c)
+constexpr int JC = CB + 32;        // [96]     J(ab).c   (pair * 2 + which c) * 8 + (a, b, c)
+constexpr int CD = JC + 96;        // [24]     c.d       pair * 4 + (c, d)
+constexpr int END1 = CD + 24;
+//   stage 2
+constexpr int J3 = R;              // [4][64]  (missing g * 2 + middle) * 8 + (a, b, c)
+constexpr int YZ = J3 + 256;       // [4][64]  side * 32 + g * 8 + (t, t~, g)
+constexpr int END2 = YZ + 256;
+//   stage 3: G(a, d), four ordered pairs at a time
+constexpr int GG = R;              // [4][64]  ordered pair * 16 + (t, t~, a, b), a < b
+//   stage 4
+constexpr int U2 = R;              // [4][96]  (pair * 2 + order) * 8 + (t, a, b)
+constexpr int W2 = U2 + 384;       // [4][96]  (pair * 2 + order) * 8 + (t~, a, b)
+constexpr int END4 = W2 + 384;
+constexpr int MAX(int a, int b) { return a > b ? a : b; }
+constexpr int LDS_UNITS = MAX(MAX(END1, END2), END4);
+
+// momentum slots: incoming momenta of gluon sets, and the momenta q along
+// the quark line of its propagators
+constexpr int K_ONE = 0;    // + g
+constexpr int K_U1 = 4;     // + g
+constexpr int K_W1 = 8;     // + g
+constexpr int K_THREE = 12; // + g missing
+constexpr int K_TWO = 16;   // + pair
+constexpr int K_FOUR = 22;
+constexpr int K_U2 = 24;    // + pair
+
+// pairs (01) (02) (03) (12) (13) (23)
+__host__ __device__ constexpr int pair_of(int a, int b) {
+  const int lo = a < b ? a : b, hi = a < b ? b : a;
+  return lo == 0 ? hi - 1 : (lo == 1 ? hi + 1 : 5);
+}
+// the same for a pair index that differs by lane
+__device__ __forceinline__ int pair_lo(int p) { return (0x940 >> (2 * p)) & 3; }
+__device__ __forceinline__ int pair_hi(int p) { return (0xFB9 >> (2 * p)) & 3; }
+// k-th (0, 1, 2) of the gluons other than g
+__host__ __device__ constexpr int other3(int g, int k) { return k + (k >= g ? 1 : 0); }
+// rank of the ordering (a b c d) in lexicographic order
+__host__ __device__ constexpr int flow(int a, int b, int c, int d) {
+  return 6 * a + 2 * (b - (b > a)) + (c > d);
+}
+
+struct Helicity {  // helicity bits (0 / 1) of a lane
+  int t, tb, g[4];
+};
+
+// The flows as they are now: what has been added to them is not put off past
+// this point (the compiler would otherwise carry the operands along and spill
+// them).
+__device__ __forceinline__ void settle(c64 (&A)[24]) {
+#pragma unroll
+  for (int k = 0; k < 24; ++k) {
+    opaque(A[k].r);
+    opaque(A[k].i);
+  }
+}
+
+// Colour flows A / g of the event with momenta p (the same in every lane) for
+// the helicity code of the lane; every lane of the wave takes part.
+__device__ __forceinline__ void flows(double (&p)[6][4], const Couplings<double>& cp, d2* lds,
+                                      int lane, c64 (&A)[24]) {
+  // ---- momenta, propagators, external wavefunctions --------------------
+  if (lane < 32) {
+    const int g = lane & 3, e = lane & 7;
+    const int gm = lane < 12 ? 1 << g : (lane < 16 ? 15 ^ (1 << g) : (0x0FCA6953 >> (4 * e)) & 15);
+    const bool top = (lane >= K_U1 && lane < K_W1) || lane >= K_U2;
+    const bool atop = lane >= K_W1 && lane < K_THREE;
+    const double c0 = gm & 1, c1 = (gm >> 1) & 1, c4 = -((gm >> 2) & 1), c5 = -((gm >> 3) & 1);
+    const double ct = top ? -1.0 : 0.0, ctb = atop ? -1.0 : 0.0;
+    double K[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+      K[m] = fmadd(c5, p[5][m], fmadd(c4, p[4][m], fmadd(ctb, p[3][m],
+             fmadd(ct, p[2][m], fmadd(c1, p[1][m], c0 * p[0][m])))));
+    const bool quark = top || atop;
+    const double wid = ((gm ^ (gm >> 1)) & 1) ? cp.wtt : cp.wt;
+    const double k2 = msq(K);
+    const double re = k2 - cp.mt * cp.mt, im = cp.mt * wid;
+    const double n = recip(quark ? re * re + im * im : k2);
+    // vectors: g / K^2; quarks: -g / (q^2 - m^2 + i m w)
+    const c64 pr = quark ? c64{-cp.gs * (re * n), cp.gs * (im * n)} : c64{cp.gs * n, 0.0};
+    const double s = top ? -1.0 : 1.0;  // q of the t side runs against K
+    lds[KV + 2 * lane] = d2{s * K[0], s * K[1]};
+    lds[KV + 2 * lane + 1] = d2{s * K[2], s * K[3]};
+    lds[PR + lane] = d2{pr.r, pr.i};
+  }
+  if (lane < 12) {
+    const int leg = lane < 4 ? lane >> 1 : (lane < 8 ? 2 + (lane >> 1) : (lane < 10 ? 2 : 3));
+    double q[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      q[m] = p[0][m];
+#pragma unroll
+      for (int l = 1; l < 6; ++l) q[m] = leg == l ? p[l][m] : q[m];
+    }
+    const int lam = (lane & 1) ? 1 : -1;
+    c64 w[4];
+    if (lane < 8) {
+      ext_vector<double>(q, lam, leg > 1, w);
+      lds_put(lds + EPS + lane, 8, w);
+    } else {
+      top_spinor(q, cp.mt, lam, leg == 3, w);
+      lds_put(lds + QV + lane - 8, 4, w);
+    }
+  }
+  __syncthreads();
+  // ---- J(ab), U(a) and W(a), B -----------------------------------------
+  if (lane < 24) {
+    const int pr = lane >> 2, a = pair_lo(pr), b = pair_hi(pr);
+    c64 x[4], y[4], o[4];
+    double kx[4], ky[4];
+    lds_get_eps(lds + EPS + 2 * a + (lane & 1), x);
+    lds_get_eps(lds + EPS + 2 * b + ((lane >> 1) & 1), y);
+    lds_get_real(lds + KV + 2 * (K_ONE + a), kx);
+    lds_get_real(lds + KV + 2 * (K_ONE + b), ky);
+    three_gluon(x, kx, y, ky, o);
+    const double f = -lds[PR + K_TWO + pr].x;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) o[m] = f * o[m];
+    lds_put(lds + J2 + lane, 24, o);
+  }
+  if (lane < 32) {
+    const int side = lane >> 4, g = (lane >> 2) & 3;
+    c64 V[4], f[4], s[4], o[4];
+    double q[4];
+    lds_get(lds + QV + 2 * side + (lane & 1), 4, s);
+    lds_get_eps(lds + EPS + 2 * g + ((lane >> 1) & 1), V);
+    const int k = (side ? K_W1 : K_U1) + g;
+    lds_get_real(lds + KV + 2 * k, q);
+    slash_col(V, s, f);
+    propagate(q, cp.mt, lds_scalar(lds + PR + k), f, o);
+    lds_put(lds + U1 + lane, 32, o);
+  } else if (lane < 36) {
+    c64 u[4], v[4], o[4];
+    lds_get(lds + QV + (lane & 1), 4, u);
+    lds_get(lds + QV + 2 + ((lane >> 1) & 1), 4, v);
+    bilinear(u, v, o);
+    lds_put(lds + BB + lane - 32, 4, o);
+  }
+  __syncthreads();
+
+  const Helicity h{(lane >> 3) & 1, (lane >> 2) & 1,
+                   {(lane >> 5) & 1, (lane >> 4) & 1, (lane >> 1) & 1, lane & 1}};
+  const int htt = h.t | (h.tb << 1);
+  const double k4 = lds[PR + K_FOUR].x;  // g / K^2 of all four gluons
+
+  // ---- stage 2: three-gluon currents -----------------------------------
+  {
+    // J(x m y) of the triple without gluon g, m its smallest or second gluon
+    const int g = lane >> 4, mid = (lane >> 3) & 1;
+    const int i0 = (g == 0), i1 = 1 + (g <= 1), i2 = 2 + (g <= 2);
+    const int h0 = lane & 1, h1 = (lane >> 1) & 1, h2 = (lane >> 2) & 1;
+    const int x = mid ? i0 : i1, m = mid ? i1 : i0, hx = mid ? h0 : h1, hm = mid ? h1 : h0;
+    c64 ex[4], em[4], ey[4], jxm[4], jmy[4], o1[4], o2[4];
+    double kx[4], ky[4], kxm[4], kmy[4];
+    lds_get_eps(lds + EPS + 2 * x + hx, ex);
+    lds_get_eps(lds + EPS + 2 * m + hm, em);
+    lds_get_eps(lds + EPS + 2 * i2 + h2, ey);
+    const int p01 = i0 == 0 ? i1 - 1 : 3;               // pair (i0 i1): (01) (02) (12)
+    const int pm2 = m == 0 ? i2 - 1 : (m == 1 ? i2 + 1 : 5);
+    lds_get(lds + J2 + 4 * p01 + h0 + 2 * h1, 24, jxm);  // J(i0 i1) = -J(x m) when m = i0
+    lds_get(lds + J2 + 4 * pm2 + hm + 2 * h2, 24, jmy);
+    lds_get_real(lds + KV + 2 * (K_ONE + x), kx);
+    lds_get_real(lds + KV + 2 * (K_ONE + i2), ky);
+    lds_get_real(lds + KV + 2 * (K_TWO + p01), kxm);
+    lds_get_real(lds + KV + 2 * (K_TWO + pm2), kmy);
+    three_gluon(jxm, kxm, ey, ky, o1);
+    three_gluon(ex, kx, jmy, kmy, o2);
+    const double s1 = mid ? -1.0 : 1.0;  // -L(J(xm), y) with the sign of J(xm)
+    const c64 xz = cp.gs * mdot0(ex, ey), yz = cp.gs * mdot0(em, ey), xy = cp.gs * mdot0(ex, em);
+    const double f = lds[PR + K_THREE + g].x;
+    c64 o[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      c64 t = rmadd(s1, o1[k], -o2[k]);
+      t = cmadd(2.0 * em[k], xz, t);
+      t = cmsub(ex[k], yz, t);
+      o[k] = f * cmsub(ey[k], xy, t);
+    }
+    lds_put(lds + J3 + lane, 64, o);
+  }
+  {
+    // Y(g) and Z(g)
+    const int side = lane >> 5, g = (lane >> 3) & 3, ht = lane & 1, hb = (lane >> 1) & 1,
+              hg = (lane >> 2) & 1;
+    c64 u[4], v[4], e[4], B[4], X[4], o[4];
+    double kg[4], kb[4];
+    // side 0: U(g) gamma v; side 1: u gamma W(g)
+    lds_get(lds + (side ? QV + ht : U1 + 4 * g + ht + 2 * hg), side ? 4 : 32, u);
+    lds_get(lds + (side ? U1 + 16 + 4 * g + hb + 2 * hg : QV + 2 + hb), side ? 32 : 4, v);
+    lds_get_eps(lds + EPS + 2 * g + hg, e);
+    lds_get(lds + BB + ht + 2 * hb, 4, B);
+    lds_get_real(lds + KV + 2 * (K_ONE + g), kg);
+    lds_get_real(lds + KV + 2 * K_FOUR, kb);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) kb[m] = -kb[m];
+    bilinear(u, v, o);
+    three_gluon(e, kg, B, kb, X);
+    const double s = side ? -k4 : k4;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) o[m] = rmadd(s, X[m], o[m]);
+    lds_put(lds + YZ + lane, 64, o);
+  }
+  __syncthreads();
+  c64 zero{0.0, 0.0};
+#pragma unroll
+  for (int k = 0; k < 24; ++k) A[k] = zero;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const int i0 = other3(g, 0), i1 = other3(g, 1), i2 = other3(g, 2);
+    const int v3 = h.g[i0] | (h.g[i1] << 1) | (h.g[i2] << 2);
+    c64 y[4], z[4], ym[3], zm[3];
+    lds_get(lds + YZ + 8 * g + htt + 4 * h.g[g], 64, y);
+    lds_get(lds + YZ + 32 + 8 * g + htt + 4 * h.g[g], 64, z);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      c64 j[4];
+      lds_get(lds + J3 + (2 * g + k) * 8 + v3, 64, j);
+      ym[k] = mdot0(j, y);
+      zm[k] = mdot0(j, z);
+    }
+    ym[2] = -(ym[0] + ym[1]);
+    zm[2] = -(zm[0] + zm[1]);
+    // flows (g x m y) and (x m y g), m the k-th gluon of the triple
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const int m = other3(g, k), x = other3(g, k == 0 ? 1 : 0), y_ = other3(g, k == 2 ? 1 : 2);
+      A[flow(g, x, m, y_)] = A[flow(g, x, m, y_)] + ym[k];
+      A[flow(g, y_, m, x)] = A[flow(g, y_, m, x)] + ym[k];
+      A[flow(x, m, y_, g)] = A[flow(x, m, y_, g)] + zm[k];
+      A[flow(y_, m, x, g)] = A[flow(y_, m, x, g)] + zm[k];
+    }
+  }
+  settle(A);
+  __syncthreads();
+  // ---- stage 1: diagrams whose quark line carries one four-gluon current,
+  // but for those counted in Y and Z
+  if (lane < 48) {
+    const int k = lane >> 4;  // pairing (01|23) (02|13) (03|12) = pairs (k | 5 - k)
+    const int a = pair_lo(k), b = pair_hi(k), c = pair_lo(5 - k), d = pair_hi(5 - k);
+    c64 x[4], y[4], o[4];
+    double kx[4], ky[4];
+    lds_get(lds + J2 + 4 * k + ((lane >> a) & 1) + 2 * ((lane >> b) & 1), 24, x);
+    lds_get(lds + J2 + 4 * (5 - k) + ((lane >> c) & 1) + 2 * ((lane >> d) & 1), 24, y);
+    lds_get_real(lds + KV + 2 * (K_TWO + k), kx);
+    lds_get_real(lds + KV + 2 * (K_TWO + 5 - k), ky);
+    three_gluon(x, kx, y, ky, o);
+    lds_put(lds + NN + lane, 48, o);
+  }
+  // scalar products of the quartic vertices, 64 at a time
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int j = lane + 64 * i;
+    int xa = BB, xn = 4, ya = BB, yn = 4;
+    if (j < 96) {                 // J(ab).B
+      xa = J2 + 4 * (j >> 4) + ((j >> 2) & 3);
+      xn = 24;
+      ya = BB + (j & 3);
+    } else if (j < 128) {         // c.B
+      const int r = j - 96;
+      xa = EPS + 2 * (r >> 3) + ((r >> 2) & 1);
+      xn = 8;
+      ya = BB + (r & 3);
+    } else if (j < 224) {         // J(ab).c
+      const int r = j - 128, pr = r >> 4, c = (r >> 3) & 1 ? pair_hi(5 - pr) : pair_lo(5 - pr);
+      xa = J2 + 4 * pr + (r & 3);
+      xn = 24;
+      ya = EPS + 2 * c + ((r >> 2) & 1);
+      yn = 8;
+    } else if (j < 248) {         // c.d
+      const int r = j - 224, pr = r >> 2;
+      xa = EPS + 2 * pair_lo(pr) + (r & 1);
+      xn = 8;
+      ya = EPS + 2 * pair_hi(pr) + ((r >> 1) & 1);
+      yn = 8;
+    }
+    c64 x[4], y[4];
+    lds_get(lds + xa, xn, x);
+    lds_get(lds + ya, yn, y);
+    const c64 s = mdot0(x, y);
+    if (j < 248) lds[JB + j] = d2{s.r, s.i};
+  }
+  __syncthreads();
+  {
+    c64 B[4], P[3], H[6][3];
+    lds_get(lds + BB + htt, 4, B);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      c64 n[4];
+      lds_get(lds + NN + 16 * k + (h.g[0] | (h.g[1] << 1) | (h.g[2] << 2) | (h.g[3] << 3)), 48, n);
+      P[k] = mdot0(n, B);
+    }
+    // H[pair][k]: quartic vertices of {J(ab), c, d} and B with J(ab) (k = 0),
+    // c (1), d (2) in the middle
+#pragma unroll
+    for (int pr = 0; pr < 6; ++pr) {
+      constexpr int LO[6] = {0, 0, 0, 1, 1, 2}, HI[6] = {1, 2, 3, 2, 3, 3};
+      const int a = LO[pr], b = HI[pr], c = LO[5 - pr], d = HI[5 - pr];
+      const int hab = h.g[a] | (h.g[b] << 1);
+      const c64 q = lds_scalar(lds + JB + 16 * pr + htt + 4 * hab) *
+                    lds_scalar(lds + CD + 4 * (5 - pr) + (h.g[c] | (h.g[d] << 1)));
+      const c64 rc = lds_scalar(lds + CB + 8 * c + htt + 4 * h.g[c]) *
+                     lds_scalar(lds + JC + (2 * pr + 1) * 8 + hab + 4 * h.g[d]);
+      const c64 rd = lds_scalar(lds + CB + 8 * d + htt + 4 * h.g[d]) *
+                     lds_scalar(lds + JC + (2 * pr) * 8 + hab + 4 * h.g[c]);
+      const c64 s = q + rc + rd;
+      H[pr][0] = rmsub(-3.0, q, -s);
+      H[pr][1] = rmsub(-3.0, rc, -s);
+      H[pr][2] = rmsub(-3.0, rd, -s);
+    }
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int d = a + 1; d < 4; ++d)
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          if (b != a && b != d) {
+            const int c = 6 - a - b - d;
+            auto sgn = [](int x, int y) { return x < y ? 1.0 : -1.0; };
+            // P(ab|cd): pairing of gluon 0, antisymmetric in each pair and in the two
+            const int k = pair_of(0, a == 0 ? b : (b == 0 ? a : (c == 0 ? d : c)));
+            const double sp = sgn(a, b) * sgn(c, d) * ((a == 0 || b == 0) ? 1.0 : -1.0);
+            // middle of V(J(ab), c, d) is c, of V(a, J(bc), d) the current, of V(a, b, J(cd)) b
+            const c64 q1 = sgn(a, b) * H[pair_of(a, b)][c < d ? 1 : 2];
+            const c64 q2 = sgn(b, c) * H[pair_of(b, c)][0];
+            const c64 q3 = sgn(c, d) * H[pair_of(c, d)][b > a ? 2 : 1];
+            const c64 e = k4 * rmsub(sp, P[k], cp.gs * (q1 + q2 + q3));
+            A[flow(a, b, c, d)] = A[flow(a, b, c, d)] + e;
+            A[flow(d, c, b, a)] = A[flow(d, c, b, a)] - e;
+          }
+  }
+  settle(A);
+  __syncthreads();
+
+  // ---- stage 3: J(bc).G(a, d) ------------------------------------------
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {  // pairs 2 i and 2 i + 1, both orders
+    settle(A);
+    __syncthreads();
+    {
+      const int o = lane >> 4, pr = 2 * i + (o >> 1), v = lane & 15;
+      const int a = (o & 1) ? pair_hi(pr) : pair_lo(pr), d = (o & 1) ? pair_lo(pr) : pair_hi(pr);
+      const int ha = (o & 1) ? (v >> 3) & 1 : (v >> 2) & 1, hd = (o & 1) ? (v >> 2) & 1 : (v >> 3) & 1;
+      c64 u[4], w[4], J[4];
+      lds_get(lds + U1 + 4 * a + (v & 1) + 2 * ha, 32, u);
+      lds_get(lds + U1 + 16 + 4 * d + ((v >> 1) & 1) + 2 * hd, 32, w);
+      bilinear(u, w, J);
+      lds_put(lds + GG + lane, 64, J);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int o = 0; o < 4; ++o) {
+      constexpr int LO[6] = {0, 0, 0, 1, 1, 2}, HI[6] = {1, 2, 3, 2, 3, 3};
+      const int pr = 2 * i + (o >> 1);
+      const int a = (o & 1) ? HI[pr] : LO[pr], d = (o & 1) ? LO[pr] : HI[pr];
+      const int b = LO[5 - pr], c = HI[5 - pr];
+      c64 J[4], G[4];
+      lds_get(lds + J2 + 4 * (5 - pr) + h.g[b] + 2 * h.g[c], 24, J);
+      lds_get(lds + GG + 16 * o + htt + 4 * h.g[LO[pr]] + 8 * h.g[HI[pr]], 64, G);
+      const c64 s = mdot0(J, G);
+      A[flow(a, b, c, d)] = A[flow(a, b, c, d)] + s;
+      A[flow(a, c, b, d)] = A[flow(a, c, b, d)] - s;
+    }
+  }
+  settle(A);
+  __syncthreads();
+  // ---- stage 4: U(ab).W(cd) --------------------------------------------
+  if (lane < 48) {
+    const int pr = lane >> 3, a = pair_lo(pr), b = pair_hi(pr);
+    const int hq = lane & 1, ha = (lane >> 1) & 1, hb = (lane >> 2) & 1;
+    c64 ea[4], eb[4], j[4];
+    lds_get_eps(lds + EPS + 2 * a + ha, ea);
+    lds_get_eps(lds + EPS + 2 * b + hb, eb);
+    lds_get(lds + J2 + 4 * pr + ha + 2 * hb, 24, j);
+    {
+      c64 s0[4], s1[4], f[4], fab[4], fba[4], o[4];
+      double q[4];
+      lds_get(lds + QV + hq, 4, s0);
+      slash_col(j, s0, f);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        fab[k] = f[k];
+        fba[k] = -f[k];
+      }
+      lds_get(lds + U1 + 4 * a + hq + 2 * ha, 32, s1);
+      slash_col_add(eb, s1, fab);
+      lds_get(lds + U1 + 4 * b + hq + 2 * hb, 32, s1);
+      slash_col_add(ea, s1, fba);
+      lds_get_real(lds + KV + 2 * (K_U2 + pr), q);
+      const c64 d = lds_scalar(lds + PR + K_U2 + pr);
+      propagate(q, cp.mt, d, fab, o);
+      lds_put(lds + U2 + 16 * pr + (lane & 7), 96, o);
+      propagate(q, cp.mt, d, fba, o);
+      lds_put(lds + U2 + 16 * pr + 8 + (lane & 7), 96, o);
+    }
+    {
+      c64 s0[4], s1[4], f[4], o[4];
+      lds_get(lds + QV + 2 + hq, 4, s0);
+      slash_col(j, s0, f);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) o[k] = f[k];
+      lds_get(lds + U1 + 16 + 4 * b + hq + 2 * hb, 32, s1);
+      slash_col_add(ea, s1, o);  // a-slash W(b) + J-slash(ab) v
+      lds_put(lds + W2 + 16 * pr + (lane & 7), 96, o);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) o[k] = -f[k];
+      lds_get(lds + U1 + 16 + 4 * a + hq + 2 * ha, 32, s1);
+      slash_col_add(eb, s1, o);
+      lds_put(lds + W2 + 16 * pr + 8 + (lane & 7), 96, o);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int pr = 0; pr < 6; ++pr) {
+    constexpr int LO[6] = {0, 0, 0, 1, 1, 2}, HI[6] = {1, 2, 3, 2, 3, 3};
+    const int a = LO[pr], b = HI[pr], c = LO[5 - pr], d = HI[5 - pr];
+    const int vu = h.t | (h.g[a] << 1) | (h.g[b] << 2), vw = h.tb | (h.g[c] << 1) | (h.g[d] << 2);
+    c64 u[2][4], w[4];
+    lds_get(lds + U2 + 16 * pr + vu, 96, u[0]);
+    lds_get(lds + U2 + 16 * pr + 8 + vu, 96, u[1]);
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+      lds_get(lds + W2 + 16 * (5 - pr) + 8 * o + vw, 96, w);
+      const int cc = o ? d : c, dd = o ? c : d;
+      A[flow(a, b, cc, dd)] = sdot_add(u[0], w, A[flow(a, b, cc, dd)]);
+      A[flow(b, a, cc, dd)] = sdot_add(u[1], w, A[flow(b, a, cc, dd)]);
+    }
+  }
+}
+
+}  // namespace ggttgg_shared
+
+// One event per wave, lane h assembling helicity h from the shared currents.
+// hel_mask: the helicities summed; mehel (or null): each helicity's value.
+template <class P>
+__global__ void __launch_bounds__(64, 2)
+    sigmakin_ggttgg_shared_kernel(const double* __restrict__ mom, int64_t nevt,
+                                  double* __restrict__ me, const double* __restrict__ wgt,
+                                  double* __restrict__ evtw, double* __restrict__ mehel,
+                                  uint64_t hel_mask, Couplings<double> c, double inv_iden) {
+  __shared__ d2 lds[ggttgg_shared::LDS_UNITS];
+  const int64_t i = xcd_event(blockIdx.x, nevt);
+  const int lane = threadIdx.x;
+  double q[P::NPAR][4];
+  load_event<P>(mom, i, q);
+  c64 A[P::NCOL];
+  ggttgg_shared::flows(q, c, lds, lane, A);
+  double v = c.gs2 * P::template colour_sum<double>(A);
+  if (mehel) mehel[(int64_t)lane * nevt + i] = v;
+  v = (hel_mask >> lane) & 1 ? v : 0.0;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  if (lane == 0) {
+    const double m = v * inv_iden;
+    if (me) me[i] = m;
+    if (evtw) evtw[i] = m * wgt[i];
+  }
+}
+
+template <class P>
+int sigmakin_ggttgg_shared_launch(const MeArgs& a, const double* mom, int64_t nevt, double* me,
+                                  const double* wgt, double* evtw, double* mehel, hipStream_t s) {
+  uint64_t mask = 0;
+  for (int k = 0; k < a.hel.n; ++k) mask |= 1ull << a.hel.code[k];
+  sigmakin_ggttgg_shared_kernel<P><<<(unsigned)nevt, 64, 0, s>>>(mom, nevt, me, wgt, evtw, mehel,
+                                                                mask, a.c64, a.inv_iden);
+  return 0;
+}
+
+}  // namespace mg

@@ -5,7 +5,10 @@
 //                            helicities inside the lane (the paper's layout);
 //   sigmakin_hpl_kernel      one event per wave, one helicity per lane (64
 //                            helicities): wave-uniform momenta in scalar
-//                            registers, helicity sum by wave reduction;
+//                            registers, helicity sum by wave reduction (FP32
+//                            amplitudes);
+//   sigmakin_ggttgg_shared_kernel  FP64, one event per wave, the currents
+//                            shared between helicities (shared_currents.h);
 //   sigmakin_mixed_kernel    event per lane with the colour sum on the
 //                            matrix cores (colour_mfma.h);
 //   sigmakin_mixed_hpl_kernel  one event per wave, one helicity per lane,
@@ -56,6 +59,10 @@ __device__ __forceinline__ void load_event(const double* __restrict__ mom, int64
 #pragma unroll
     for (int m = 0; m < 4; ++m) p[ip][m] = mom[aosoa_mom(i, ip, m, P::NPAR)];
 }
+
+}  // namespace mg
+#include "shared_currents.h"
+namespace mg {
 
 // The momenta of event i for one pass of a helicity loop.  With REREAD they
 // are read again (cache hits) through an event index the compiler cannot see

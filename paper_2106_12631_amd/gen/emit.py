@@ -1074,8 +1074,9 @@ def emit_units(name):
         if hpl:
             body = (f'#ifdef MG_EVENT_PER_LANE_{prec.upper()}\n'
                     f'  return sigmakin_launch<P_{name}, {T}, 64>(a, a.{c}, mom, nevt, me, wgt, evtw, mehel, s);\n'
-                    f'#else\n'
-                    f'  return sigmakin_hpl_launch<P_{name}, {T}, 64>(a, a.{c}, mom, nevt, me, wgt, evtw, mehel, s);\n'
+                    f'#else\n' + (f'  return sigmakin_{name}_shared_launch<P_{name}>(a, mom, nevt, me, wgt, evtw, mehel, s);\n'
+                       if prec == 'f64' else
+                       f'  return sigmakin_hpl_launch<P_{name}, {T}, 64>(a, a.{c}, mom, nevt, me, wgt, evtw, mehel, s);\n') +
                     f'#endif\n')
         else:
             body = f'  return {epl};\n'
