@@ -123,25 +123,95 @@ __device__ __forceinline__ void three_gluon(const c64 (&x)[4], const double (&kx
   for (int m = 0; m < 4; ++m) out[m] = rmadd(dk[m], xy, cmadd(y[m], cy_, x[m] * cx_));
 }
 
-// Spinors of the t (mapped to a column) and the t~: ubar(p, lam) of helas.h
-// mapped, or v(p, lam), one branch-free body for the lanes of both
-__device__ __forceinline__ void top_spinor(const double (&p)[4], double m, int lam, bool anti,
-                                           c64 (&w)[4]) {
-  double wm, wp, c0r, c0i, c1r, c1i;
-  omegas(p, m, lam, wm, wp);
-  helicity_chi(p, anti ? -lam : lam, c0r, c0i, c1r, c1i);
-  const c64 a0{wp * c0r, wp * c0i}, a1{wp * c1r, wp * c1i};
-  const c64 b0{wm * c0r, wm * c0i}, b1{wm * c1r, wm * c1i};
-  if (anti) {  // (wp chi, -wm chi)
-    w[0] = a0;
-    w[1] = a1;
-    w[2] = -b0;
-    w[3] = -b1;
-  } else {     // row (wp chi^+, wm chi^+) as the column (f1, -f0, f3, -f2)
-    w[0] = conj(a1);
-    w[1] = -conj(a0);
-    w[2] = conj(b1);
-    w[3] = -conj(b0);
+// Sum over the 64 lanes, in every lane, without LDS: exchanges inside quads
+// and rows of 16 by DPP, then of 16- and 32-lane halves.
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double x) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, x);
+  const unsigned lo = __builtin_amdgcn_mov_dpp((int)(unsigned)b, CTRL, 0xF, 0xF, true);
+  const unsigned hi = __builtin_amdgcn_mov_dpp((int)(unsigned)(b >> 32), CTRL, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  v += dpp_move<0xB1>(v);   // quad_perm 1 0 3 2
+  v += dpp_move<0x4E>(v);   // quad_perm 2 3 0 1
+  v += dpp_move<0x141>(v);  // row_half_mirror
+  v += dpp_move<0x140>(v);  // row_mirror
+  unsigned lo, hi;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    lo = (unsigned)b;
+    hi = (unsigned)(b >> 32);
+    // swap(x, x) returns (x of the lower halves in both, x of the upper ones)
+    const auto rl = k ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false)
+                      : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto rh = k ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false)
+                      : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    v = __builtin_bit_cast(double, (uint64_t)rl[0] | ((uint64_t)rh[0] << 32)) +
+        __builtin_bit_cast(double, (uint64_t)rl[1] | ((uint64_t)rh[1] << 32));
+  }
+  return v;
+}
+
+// 1 / sqrt(x), x > 0: the hardware estimate and two Newton steps (within an
+// ulp or two)
+__device__ __forceinline__ double rsqrt_refined(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const double e = fmadd(-x * y, y, 1.0);
+    y = fmadd(0.5 * y, e, y);
+  }
+  return y;
+}
+
+// External wavefunctions of helas.h (ext_vector; ext_u barred, mapped to a
+// column; ext_v), in one body for lanes that hold different legs: the roots
+// and reciprocals that both kinds need are formed once, from reciprocal
+// square roots.
+__device__ __forceinline__ void external(const double (&p)[4], double m, int lam, bool gluon,
+                                         bool flag, c64 (&w)[4]) {
+  const double pt2 = p[1] * p[1] + p[2] * p[2];
+  const double P2 = pt2 + p[3] * p[3];
+  const double iP = rsqrt_refined(P2);
+  const double P = P2 > 0.0 ? P2 * iP : 0.0;
+  const double epp = p[0] + P;
+  const double x = gluon ? (pt2 > 0.0 ? pt2 : 1.0) : epp;
+  const double ix = rsqrt_refined(x);
+  if (gluon) {  // flag: outgoing
+    const double r2 = 0.70710678118654752440;
+    const double a = -lam * r2, b = flag ? r2 : -r2;
+    const double cph = pt2 > 0.0 ? p[1] * ix : 1.0, sph = pt2 > 0.0 ? p[2] * ix : 0.0;
+    const double kt = pt2 * ix;
+    const double cth = p[3] * iP;
+    w[0] = c64{0.0, 0.0};
+    w[1] = c64{a * cth * cph, -b * sph};
+    w[2] = c64{a * cth * sph, b * cph};
+    w[3] = c64{-a * (kt * iP), 0.0};
+  } else {      // flag: the t~
+    const double big = epp * ix, small = m * ix;  // sqrt(E + P), sqrt(E - P)
+    const double ppz = p[3] >= 0.0 ? P + p[3] : pt2 * recip(P - p[3]);
+    const bool back = !(ppz > 0.0);
+    const double nrm = rsqrt_refined(back ? 1.0 : 2.0 * P * ppz);
+    // chi+ = (c, x + i y), chi- = (-x + i y, c); along -z (0, 1), (-1, 0)
+    const double c = back ? 0.0 : ppz * nrm;
+    const double cx_ = back ? 1.0 : p[1] * nrm, cy_ = back ? 0.0 : p[2] * nrm;
+    const bool up = (lam > 0) != flag;  // the t~ has the spinor of the opposite helicity
+    const c64 c0 = up ? c64{c, 0.0} : c64{-cx_, cy_}, c1 = up ? c64{cx_, cy_} : c64{c, 0.0};
+    const double wp = lam > 0 ? big : small, wm = lam > 0 ? small : big;
+    const c64 a0 = wp * c0, a1 = wp * c1, b0 = wm * c0, b1 = wm * c1;
+    if (flag) {  // (wp chi, -wm chi)
+      w[0] = a0;
+      w[1] = a1;
+      w[2] = -b0;
+      w[3] = -b1;
+    } else {     // row (wp chi^+, wm chi^+) as the column (f1, -f0, f3, -f2)
+      w[0] = conj(a1);
+      w[1] = -conj(a0);
+      w[2] = conj(b1);
+      w[3] = -conj(b0);
+    }
   }
 }
 
@@ -161,10 +231,13 @@ __device__ __forceinline__ void top_spinor(const double (&p)[4], double m, int l
 //
 // The currents are built by the lanes side by side (a lane per current and
 // helicity version) and handed on through LDS; then lane h assembles the 24
-// flows of helicity h.  Bound: FP64 VALU (busy 80 % of the time, two waves per
-// SIMD of 229 registers and 18 KB of LDS each): 4.0e3 VALU instructions per
-// event in place of 18.3e3 with one full amplitude per lane; 2^19 events in
-// 4.4 ms, 119 M events/s (19.3 ms, 27.2 M with one full amplitude per lane).
+// flows of helicity h.  Bound: LDS bandwidth (515 accesses of 16 bytes a lane
+// at 128 bytes/clock: 4.1e3 of the 4.3e3 clocks per event and CU) close to the
+// FP64 VALU (3.3e3 instructions per event; 18.3e3 with one full amplitude per
+// lane).  Two waves per SIMD: 232 registers, 18 KB of LDS a wave.  2^19 events
+// in 3.71 ms, 141 M events/s (19.05 ms with one full amplitude per lane; 4.40
+// before the block-form colour sum, the external wavefunctions from refined
+// reciprocal roots and the DPP helicity sum).
 namespace ggttgg_shared {
 
 // LDS in units of one complex (16 bytes); versions are bit fields of the
@@ -178,9 +251,9 @@ constexpr int U1 = J2 + 96;        // [4][32]  side * 16 + g * 4 + (quark, g)
 constexpr int BB = U1 + 128;       // [4][4]   (t, t~)
 constexpr int R = BB + 16;         // reused by the stages
 //   stage 1
-constexpr int NN = R;              // [4][48]  pairing * 16 + (0, 1, 2, 3)
-constexpr int JB = NN + 192;       // [96]     J(ab).B   pair * 16 + (t, t~, a, b)
-constexpr int CB = JB + 96;        // [32]     c.B       g * 8 + (t, t~, c)
+constexpr int NN = R;              // [4][48]  g/K^2 L(J(ab), J(cd))  pairing * 16 + (0, 1, 2, 3)
+constexpr int JB = NN + 192;       // [96]     g^2/K^2 J(ab).B  pair * 16 + (t, t~, a, b)
+constexpr int CB = JB + 96;        // [32]     g^2/K^2 c.B     g * 8 + (t, t~, c)
 constexpr int JC = CB + 32;        // [96]     J(ab).c   (pair * 2 + which c) * 8 + (a, b, c)
 constexpr int CD = JC + 96;        // [24]     c.d       pair * 4 + (c, d)
 constexpr int END1 = CD + 24;
@@ -237,11 +310,22 @@ __device__ __forceinline__ void settle(c64 (&A)[24]) {
   }
 }
 
-// Colour flows A / g of the event with momenta p (the same in every lane) for
-// the helicity code of the lane; every lane of the wave takes part.
-__device__ __forceinline__ void flows(double (&p)[6][4], const Couplings<double>& cp, d2* lds,
-                                      int lane, c64 (&A)[24]) {
+// Colour flows A / g of event i (the same in every lane) for the helicity
+// code of the lane; every lane of the wave takes part.
+template <class P>
+__device__ __forceinline__ void flows(const double* __restrict__ mom, int64_t i,
+                                      const Couplings<double>& cp, d2* lds, int lane,
+                                      c64 (&A)[24]) {
   // ---- momenta, propagators, external wavefunctions --------------------
+  double p[6][4];
+  load_event<P>(mom, i, p);
+  // lanes 0..7: gluons, 8..11: t and t~, each with both helicities
+  const int leg = lane < 4 ? lane >> 1 : (lane < 8 ? 2 + (lane >> 1) : (lane < 10 ? 2 : 3));
+  double q[4];
+  if (lane < 12) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) q[m] = mom[aosoa_mom(i, 0, m, 6) + leg * 4 * NEPPM];
+  }
   if (lane < 32) {
     const int g = lane & 3, e = lane & 7;
     const int gm = lane < 12 ? 1 << g : (lane < 16 ? 15 ^ (1 << g) : (0x0FCA6953 >> (4 * e)) & 15);
@@ -267,23 +351,10 @@ __device__ __forceinline__ void flows(double (&p)[6][4], const Couplings<double>
     lds[PR + lane] = d2{pr.r, pr.i};
   }
   if (lane < 12) {
-    const int leg = lane < 4 ? lane >> 1 : (lane < 8 ? 2 + (lane >> 1) : (lane < 10 ? 2 : 3));
-    double q[4];
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      q[m] = p[0][m];
-#pragma unroll
-      for (int l = 1; l < 6; ++l) q[m] = leg == l ? p[l][m] : q[m];
-    }
     const int lam = (lane & 1) ? 1 : -1;
     c64 w[4];
-    if (lane < 8) {
-      ext_vector<double>(q, lam, leg > 1, w);
-      lds_put(lds + EPS + lane, 8, w);
-    } else {
-      top_spinor(q, cp.mt, lam, leg == 3, w);
-      lds_put(lds + QV + lane - 8, 4, w);
-    }
+    external(q, cp.mt, lam, lane < 8, lane < 8 ? leg > 1 : leg == 3, w);
+    lds_put(lds + (lane < 8 ? EPS + lane : QV + lane - 8), lane < 8 ? 8 : 4, w);
   }
   __syncthreads();
   // ---- J(ab), U(a) and W(a), B -----------------------------------------
@@ -427,50 +498,51 @@ __device__ __forceinline__ void flows(double (&p)[6][4], const Couplings<double>
     lds_get_real(lds + KV + 2 * (K_TWO + k), kx);
     lds_get_real(lds + KV + 2 * (K_TWO + 5 - k), ky);
     three_gluon(x, kx, y, ky, o);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) o[m] = k4 * o[m];
     lds_put(lds + NN + lane, 48, o);
   }
-  // scalar products of the quartic vertices, 64 at a time
+  // scalar products of the quartic vertices, 64 at a time: J(ab).B of the
+  // pairs 0..3; of the pairs 4, 5 and c.B; J(ab).c of the pairs 0..3; of the
+  // pairs 4, 5 and c.d
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int j = lane + 64 * i;
-    int xa = BB, xn = 4, ya = BB, yn = 4;
-    if (j < 96) {                 // J(ab).B
-      xa = J2 + 4 * (j >> 4) + ((j >> 2) & 3);
-      xn = 24;
-      ya = BB + (j & 3);
-    } else if (j < 128) {         // c.B
-      const int r = j - 96;
-      xa = EPS + 2 * (r >> 3) + ((r >> 2) & 1);
-      xn = 8;
-      ya = BB + (r & 3);
-    } else if (j < 224) {         // J(ab).c
-      const int r = j - 128, pr = r >> 4, c = (r >> 3) & 1 ? pair_hi(5 - pr) : pair_lo(5 - pr);
-      xa = J2 + 4 * pr + (r & 3);
-      xn = 24;
-      ya = EPS + 2 * c + ((r >> 2) & 1);
+    const int l = lane & 31, hi = lane >> 5;
+    int xa, xn = 24, ya, yn;
+    if (i < 2) {
+      const int pr = lane >> 4, xj = J2 + 4 * pr + ((lane >> 2) & 3);
+      xa = i == 0 ? xj : (hi ? EPS + 2 * (l >> 3) + ((l >> 2) & 1) : xj + 16);
+      if (i == 1) xn = hi ? 8 : 24;
+      ya = BB + (lane & 3);
+      yn = 4;
+    } else {
+      const int pr = i == 2 ? lane >> 4 : 4 + (l >> 4), cd = l >> 2;
+      const int c = (lane >> 3) & 1 ? pair_hi(5 - pr) : pair_lo(5 - pr);
+      xa = J2 + 4 * pr + (lane & 3);
+      ya = EPS + 2 * c + ((lane >> 2) & 1);
       yn = 8;
-    } else if (j < 248) {         // c.d
-      const int r = j - 224, pr = r >> 2;
-      xa = EPS + 2 * pair_lo(pr) + (r & 1);
-      xn = 8;
-      ya = EPS + 2 * pair_hi(pr) + ((r >> 1) & 1);
-      yn = 8;
+      if (i == 3) {
+        xa = hi ? EPS + 2 * pair_lo(cd) + (l & 1) : xa;
+        ya = hi ? EPS + 2 * pair_hi(cd) + ((l >> 1) & 1) : ya;
+        xn = hi ? 8 : 24;
+      }
     }
     c64 x[4], y[4];
     lds_get(lds + xa, xn, x);
     lds_get(lds + ya, yn, y);
-    const c64 s = mdot0(x, y);
-    if (j < 248) lds[JB + j] = d2{s.r, s.i};
+    // the products with B carry the factor g^2 / K^2
+    const c64 s = (i < 2 ? cp.gs * k4 : 1.0) * mdot0(x, y);
+    if (i < 3 || lane < 56) lds[JB + lane + 64 * i] = d2{s.r, s.i};
   }
   __syncthreads();
   {
-    c64 B[4], P[3], H[6][3];
+    c64 B[4], N[3], H[6][3];
     lds_get(lds + BB + htt, 4, B);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       c64 n[4];
       lds_get(lds + NN + 16 * k + (h.g[0] | (h.g[1] << 1) | (h.g[2] << 2) | (h.g[3] << 3)), 48, n);
-      P[k] = mdot0(n, B);
+      N[k] = mdot0(n, B);
     }
     // H[pair][k]: quartic vertices of {J(ab), c, d} and B with J(ab) (k = 0),
     // c (1), d (2) in the middle
@@ -506,7 +578,7 @@ __device__ __forceinline__ void flows(double (&p)[6][4], const Couplings<double>
             const c64 q1 = sgn(a, b) * H[pair_of(a, b)][c < d ? 1 : 2];
             const c64 q2 = sgn(b, c) * H[pair_of(b, c)][0];
             const c64 q3 = sgn(c, d) * H[pair_of(c, d)][b > a ? 2 : 1];
-            const c64 e = k4 * rmsub(sp, P[k], cp.gs * (q1 + q2 + q3));
+            const c64 e = q1 + q2 + (q3 - sp * N[k]);
             A[flow(a, b, c, d)] = A[flow(a, b, c, d)] + e;
             A[flow(d, c, b, a)] = A[flow(d, c, b, a)] - e;
           }
@@ -623,15 +695,11 @@ __global__ void __launch_bounds__(64, 2)
   __shared__ d2 lds[ggttgg_shared::LDS_UNITS];
   const int64_t i = xcd_event(blockIdx.x, nevt);
   const int lane = threadIdx.x;
-  double q[P::NPAR][4];
-  load_event<P>(mom, i, q);
   c64 A[P::NCOL];
-  ggttgg_shared::flows(q, c, lds, lane, A);
-  double v = c.gs2 * P::template colour_sum<double>(A);
+  ggttgg_shared::flows<P>(mom, i, c, lds, lane, A);
+  double v = c.gs2 * P::colour_sum_blocks(A);
   if (mehel) mehel[(int64_t)lane * nevt + i] = v;
-  v = (hel_mask >> lane) & 1 ? v : 0.0;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  v = wave_sum((hel_mask >> lane) & 1 ? v : 0.0);
   if (lane == 0) {
     const double m = v * inv_iden;
     if (me) me[i] = m;

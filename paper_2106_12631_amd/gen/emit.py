@@ -91,6 +91,67 @@ def colour_mfma_tables(cnum, ncol):
     return f32, bf16
 
 
+def colour_blocks(basis, cnum):
+    """The colour matrix of the orderings `basis` of four gluons (numerators
+    cnum) brought to block form by three commuting symmetries: the exchanges of the first two
+    and of the last two gluon labels, and the reversal of an ordering.  Sums
+    and differences of the flows that a symmetry exchanges (butterflies) do not
+    mix in the quadratic form.  Returns (butterflies, matrix, scale): a list of
+    (i, j, s), variables i, j <- i + s j, i - s j in place, and the integer
+    symmetric matrix D with  sum C_ij x_i x_j = sum D_ij y_i y_j / scale."""
+    import numpy as np
+    n = len(basis)
+    index = {w: k for k, w in enumerate(basis)}
+    legs = sorted(basis[0])
+
+    def swap(a, b):
+        return [index[tuple(b if x == a else a if x == b else x for x in w)] for w in basis]
+    perms = [swap(legs[0], legs[1]), swap(legs[-2], legs[-1]),
+             [index[tuple(reversed(w))] for w in basis]]
+    C = np.array(cnum, dtype=np.int64)
+    V = np.eye(n, dtype=np.int64)      # row k: variable k in terms of the flows
+    fly = []
+    for g in perms:
+        assert (C[np.ix_(g, g)] == C).all(), "not a symmetry of the colour matrix"
+        done = set()
+        for i in range(n):
+            if i in done:
+                continue
+            img = np.zeros(n, dtype=np.int64)
+            img[g] = V[i]
+            j, s = next((j, s) for j in range(n) for s in (1, -1) if (V[j] * s == img).all())
+            done |= {i, j}
+            if j != i:
+                V[i], V[j] = V[i] + s * V[j], V[i] - s * V[j]
+                fly.append((i, j, s))
+    scale = 64
+    inv = np.linalg.inv(V.astype(float))
+    D = np.rint(scale * (inv.T @ C @ inv)).astype(np.int64)
+    assert (V.T @ D @ V == scale * C).all()
+    return fly, D.tolist(), scale
+
+
+def emit_colour_blocks(basis, cnum, cden):
+    """colour_sum in the block form of colour_blocks, for FP64."""
+    fly, D, scale = colour_blocks(basis, cnum)
+    n = len(basis)
+    L = ["// the colour sum in the block form of the colour matrix: sums and differences",
+         "// of the flows that its symmetries exchange do not mix",
+         f"__device__ __forceinline__ double colour_sum_blocks(cx<double> (&J)[{n}]) {{"]
+    for i, j, s in fly:
+        a, b = ('+', '-') if s > 0 else ('-', '+')
+        L.append(f"  {{ const cx<double> a = J[{i}], b = J[{j}]; J[{i}] = a {a} b; J[{j}] = a {b} b; }}")
+    L.append("  double me = 0.0;")
+    for i in range(n):
+        for part in 'ri':
+            t = [f"{float(D[i][j] * (1 if i == j else 2))!r} * J[{j}].{part}"
+                 for j in range(i, n) if D[i][j]]
+            L.append(f"  me = fmadd(J[{i}].{part}, {' + '.join(t)}, me);")
+    L.append(f"  return me * {1.0 / (cden * scale)!r};")
+    L.append("}")
+    return L
+
+
 def _deps(n):
     return [c for c in n.op[1:] if hasattr(c, 'idx')]
 
@@ -956,6 +1017,8 @@ def generate(name, orders=None):
         cs_flops += 2 * (2 * len(terms_r) - 1) + 4
     w(f"  return me * (T){1.0 / cden!r};")
     w("}")
+    if len(pd.gluons) == 4:
+        L.extend(emit_colour_blocks(basis, cnum, cden))
     A = []
     if name in GRAD_PROCESSES:
         for prec, T, Ct in (('a64', 'double', 'double'), ('a32', 'float', 'float')):
@@ -1063,7 +1126,10 @@ def emit_units(name):
   __device__ static __forceinline__ T colour_sum(const cx<T> (&J)[NCOL]) {{
     return gen_{name}::colour_sum<T>(J);
   }}
-}};
+''' + (f'''  __device__ static __forceinline__ double colour_sum_blocks(cx<double> (&J)[NCOL]) {{
+    return gen_{name}::colour_sum_blocks(J);
+  }}
+''' if hpl else '') + '''};
 '''
     sk_args = '(const MeArgs& a, const double* mom, int64_t nevt, double* me, const double* wgt,\n' \
               '    double* evtw, double* mehel, hipStream_t s)'
