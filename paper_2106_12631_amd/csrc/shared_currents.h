@@ -707,13 +707,509 @@ __global__ void __launch_bounds__(64, 2)
   }
 }
 
+// ---------------------------------------------------------------------------
+// e+ e- -> mu+ mu-, g g -> t t~ and g g -> t t~ g: in one lane's registers
+// ---------------------------------------------------------------------------
+// e+ e- -> mu+ mu- and g g -> t t~ take one event per lane with all helicities
+// unrolled: 2^24 events of the first in 0.46 ms (5.5 TB/s, HBM bound; 1.07 ms
+// with one amplitude per helicity), 1000003 events of the second in 52 us
+// (340 us; 75 us at one wave per SIMD, without the 36 bytes of scratch that
+// two cost).  For g g -> t t~ g that body is 1.6e5 bytes of code and spills
+// (2^20 events 1.46 ms); eight lanes per event, one for each helicity of the
+// gluons, repeat the work that one gluon's helicity would not change but need
+// no loop: 1.02 ms (2.15 ms with one amplitude per helicity).  Bound there:
+// FP64 VALU at one wave per SIMD, busy 70 % of the time.
+//
+// One object per event holds what no helicity changes (momenta along the
+// quark line, propagators, the spinors of both quark helicities); flows_sum
+// then takes the gluon helicities and hands the colour-summed |M|^2 of the
+// four quark helicities to `emit(t, t~, value)`.  With BEAM the incoming
+// gluons run along +z and -z: their polarisation vectors are (0, x, i y, 0)
+// with x, y = +-1/sqrt(2), so that slashes and products with them fold to a
+// few terms, to a single one where the helicity is known at compile time.
+
+// Helicity states of the direction of p, chi+ = (c, x + i y) and
+// chi- = (-x + i y, c), and sqrt(E + P), sqrt(E - P) = m / sqrt(E + P).
+// AXIS = +1 / -1: the momentum is along +z / -z, 0: any
+template <int AXIS>
+__device__ __forceinline__ void helicity_states(const double (&p)[4], double m, double& c,
+                                                double& x, double& y, double& big,
+                                                double& small) {
+  const double pt2 = p[1] * p[1] + p[2] * p[2];
+  const double P2 = pt2 + p[3] * p[3];
+  const double P = AXIS ? AXIS * p[3] : (P2 > 0.0 ? P2 * rsqrt_refined(P2) : 0.0);
+  const double epp = p[0] + P, ir = rsqrt_refined(epp);
+  big = epp * ir;
+  small = m * ir;
+  if constexpr (AXIS != 0) {
+    c = AXIS > 0 ? 1.0 : 0.0;
+    x = AXIS > 0 ? 0.0 : 1.0;
+    y = 0.0;
+  } else {
+    const double ppz = p[3] >= 0.0 ? P + p[3] : pt2 * recip(P - p[3]);
+    const bool back = !(ppz > 0.0);  // along -z
+    const double nrm = rsqrt_refined(back ? 1.0 : 2.0 * P * ppz);
+    c = back ? 0.0 : ppz * nrm;
+    x = back ? 1.0 : p[1] * nrm;
+    y = back ? 0.0 : p[2] * nrm;
+  }
+}
+
+// ubar (side t, mapped to a column) or v (t~) for both helicities
+__device__ __forceinline__ void quark_spinors(const double (&p)[4], double m, bool anti,
+                                              c64 (&w)[2][4]) {
+  double c, x, y, big, small;
+  helicity_states<0>(p, m, c, x, y, big, small);
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const bool up = (h == 1) != anti;
+    const double wp = h ? big : small, wm = h ? small : big;
+    const c64 c0 = up ? c64{c, 0.0} : c64{-x, y}, c1 = up ? c64{x, y} : c64{c, 0.0};
+    if (anti) {
+      w[h][0] = wp * c0;
+      w[h][1] = wp * c1;
+      w[h][2] = -(wm * c0);
+      w[h][3] = -(wm * c1);
+    } else {
+      w[h][0] = wp * conj(c1);
+      w[h][1] = -(wp * conj(c0));
+      w[h][2] = wm * conj(c1);
+      w[h][3] = -(wm * conj(c0));
+    }
+  }
+}
+
+// polarisation vector (ext_vector of helas.h); AXIS = +1 / -1: the momentum
+// is along +z / -z, 0: any
+template <int AXIS>
+__device__ __forceinline__ void polarisation(const double (&p)[4], int lam, bool conjugate,
+                                             c64 (&w)[4]) {
+  const double r2 = 0.70710678118654752440;
+  const double a = -lam * r2, b = conjugate ? r2 : -r2;
+  w[0] = c64{0.0, 0.0};
+  if constexpr (AXIS != 0) {
+    w[1] = c64{AXIS * a, 0.0};
+    w[2] = c64{0.0, b};
+    w[3] = c64{0.0, 0.0};
+  } else {
+    const double pt2 = p[1] * p[1] + p[2] * p[2];
+    const double iP = rsqrt_refined(pt2 + p[3] * p[3]);
+    const bool pt = pt2 > 0.0;
+    const double ikt = rsqrt_refined(pt ? pt2 : 1.0);
+    const double cph = pt ? p[1] * ikt : 1.0, sph = pt ? p[2] * ikt : 0.0;
+    const double cth = p[3] * iP;
+    w[1] = c64{a * cth * cph, -b * sph};
+    w[2] = c64{a * cth * sph, b * cph};
+    w[3] = c64{-a * (pt2 * ikt * iP), 0.0};
+  }
+}
+
+// -g / (q^2 - m^2 + i m w)
+__device__ __forceinline__ c64 quark_factor(const double (&q)[4], double m, double w, double g) {
+  const double re = msq(q) - m * m, im = m * w;
+  const double n = g * recip(re * re + im * im);
+  return c64{-re * n, im * n};
+}
+
+// sum and difference of incoming momenta along the quark line
+__device__ __forceinline__ void minus4(const double (&a)[4], const double (&b)[4],
+                                       double (&o)[4]) {
+#pragma unroll
+  for (int m = 0; m < 4; ++m) o[m] = a[m] - b[m];
+}
+__device__ __forceinline__ void plus4(const double (&a)[4], const double (&b)[4],
+                                      double (&o)[4]) {
+#pragma unroll
+  for (int m = 0; m < 4; ++m) o[m] = a[m] + b[m];
+}
+
+// Spinors of both helicities as they are now: what follows is computed from
+// them in place, not merged across or hoisted out of a helicity loop and kept
+// live (and the scheduler keeps the two sides apart).
+__device__ __forceinline__ void hold(c64 (&w)[2][4]) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) opaque4(w[h]);
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+template <bool BEAM, class Sum>
+struct GGTT {
+  c64 u[2][4], v[2][4], d[2];
+  double k0[4], k1[4], q[2][4], f01;
+  Couplings<double> cp;
+
+  __device__ __forceinline__ GGTT(const double (&p)[4][4], const Couplings<double>& c) : cp(c) {
+    quark_spinors(p[2], c.mt, false, u);
+    quark_spinors(p[3], c.mt, true, v);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      k0[m] = p[0][m];
+      k1[m] = p[1][m];
+    }
+    double K[4];
+    plus4(k0, k1, K);
+    f01 = c.gs * recip(msq(K));
+    minus4(k0, p[3], q[0]);
+    minus4(k1, p[3], q[1]);
+#pragma unroll
+    for (int a = 0; a < 2; ++a) d[a] = quark_factor(q[a], c.mt, c.wtt, c.gs);
+  }
+
+  // flows (01), (10):  A / g = u a-slash W(b) + u J-slash(ab) v
+  template <class Emit>
+  __device__ __forceinline__ void flows_sum(int lam0, int lam1, Emit emit) {
+    c64 e[2][4], J[4];
+    hold(v);
+    polarisation<BEAM ? 1 : 0>(k0, lam0, false, e[0]);
+    polarisation<BEAM ? -1 : 0>(k1, lam1, false, e[1]);
+    three_gluon(e[0], k0, e[1], k1, J);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) J[m] = -f01 * J[m];
+#pragma unroll
+    for (int tb = 0; tb < 2; ++tb) {
+      c64 W[2][4], s[4], R[2][4];
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        slash_col(e[a], v[tb], s);
+        propagate(q[a], cp.mt, d[a], s, W[a]);
+      }
+      slash_col(J, v[tb], s);
+      slash_col(e[0], W[1], R[0]);
+      slash_col(e[1], W[0], R[1]);
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        R[0][m] = R[0][m] + s[m];
+        R[1][m] = R[1][m] - s[m];
+      }
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const c64 z{0.0, 0.0};
+        const c64 A[2] = {sdot_add(u[t], R[0], z), sdot_add(u[t], R[1], z)};
+        emit(t, tb, cp.gs2 * Sum::sum(A));
+      }
+    }
+  }
+};
+
+template <bool BEAM, class Sum>
+struct GGTTG {
+  c64 u[2][4], v[2][4], dU[3], dW[3];
+  double k[3][4], pt[4], pb[4], f[3], f012;  // f[c]: g / K^2 of the pair without c
+  Couplings<double> cp;
+
+  __device__ __forceinline__ GGTTG(const double (&p)[5][4], const Couplings<double>& c) : cp(c) {
+    quark_spinors(p[2], c.mt, false, u);
+    quark_spinors(p[3], c.mt, true, v);
+    double K[4], K3[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      k[0][m] = p[0][m];
+      k[1][m] = p[1][m];
+      k[2][m] = -p[4][m];
+      pt[m] = p[2][m];
+      pb[m] = p[3][m];
+    }
+    plus4(k[0], k[1], K);
+    f[2] = c.gs * recip(msq(K));
+    plus4(K, k[2], K3);
+    f012 = c.gs * recip(msq(K3));
+    plus4(k[0], k[2], K);
+    f[1] = c.gs * recip(msq(K));
+    plus4(k[1], k[2], K);
+    f[0] = c.gs * recip(msq(K));
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const double w = a < 2 ? c.wtt : c.wt;
+      minus4(p[2], k[a], K);
+      dU[a] = quark_factor(K, c.mt, w, c.gs);
+      minus4(k[a], p[3], K);
+      dW[a] = quark_factor(K, c.mt, w, c.gs);
+    }
+  }
+
+  // park: this lane's slots for U(a), component k of slot s at [256 s + 64 k].
+  // A(abc) / g = U(a).(b-slash W(c) + J-slash(bc) v) + u.(J-slash(ab) W(c) + J-slash(abc) v)
+  template <class Emit>
+  __device__ __forceinline__ void flows_sum(int lam0, int lam1, int lam2, d2* park, Emit emit) {
+    c64 e[3][4], J[3][4], M[2][4];  // J[c]: the pair without c; M[m]: J(x m y), m in the middle
+    polarisation<BEAM ? 1 : 0>(k[0], lam0, false, e[0]);
+    polarisation<BEAM ? -1 : 0>(k[1], lam1, false, e[1]);
+    {
+      double p4[4];
+#pragma unroll
+      for (int m = 0; m < 4; ++m) p4[m] = -k[2][m];
+      polarisation<0>(p4, lam2, true, e[2]);
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const int a = c == 0 ? 1 : 0, b = c == 2 ? 1 : 2;
+      three_gluon(e[a], k[a], e[b], k[b], J[c]);
+#pragma unroll
+      for (int m = 0; m < 4; ++m) J[c][m] = -f[c] * J[c][m];
+    }
+    {
+      c64 L1[4], L2[4], L3[4];
+      double K[4];
+      plus4(k[0], k[1], K);
+      three_gluon(J[2], K, e[2], k[2], L1);
+      plus4(k[1], k[2], K);
+      three_gluon(e[0], k[0], J[0], K, L2);
+      plus4(k[0], k[2], K);
+      three_gluon(e[1], k[1], J[1], K, L3);
+      const c64 d01 = cp.gs * mdot0(e[0], e[1]), d02 = cp.gs * mdot0(e[0], e[2]),
+                d12 = cp.gs * mdot0(e[1], e[2]);
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        M[0][m] = f012 * cmadd(2.0 * e[0][m], d12,
+                               cmsub(e[1][m], d02, cmsub(e[2][m], d01, L1[m] - L3[m])));
+        M[1][m] = f012 * cmadd(2.0 * e[1][m], d02,
+                               cmsub(e[0][m], d12, cmsub(e[2][m], d01, -(L1[m] + L2[m]))));
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        c64 s[4], o[4];
+        double q[4];
+        slash_col(e[a], u[t], s);
+        minus4(pt, k[a], q);
+        propagate(q, cp.mt, dU[a], s, o);
+        lds_put(park + (t * 3 + a) * 256, 64, o);
+      }
+    auto of_antiquark = [&](int tb) {
+      __builtin_amdgcn_sched_barrier(0);
+      c64 W[3][4], A[2][6], s[4], r[4];
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        slash_col(e[a], v[tb], s);
+        double q[4];
+        minus4(k[a], pb, q);
+        propagate(q, cp.mt, dW[a], s, W[a]);
+      }
+      // ordering (a b c): rank 2 a + (b > c)
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        const int b = a == 0 ? 1 : 0, c = a == 2 ? 1 : 2;
+        c64 U[2][4];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) lds_get(park + (t * 3 + a) * 256, 64, U[t]);
+        slash_col(J[a], v[tb], s);
+#pragma unroll
+        for (int m = 0; m < 4; ++m) r[m] = s[m];
+        slash_col_add(e[b], W[c], r);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) A[t][2 * a] = sdot_add(U[t], r, c64{0.0, 0.0});
+#pragma unroll
+        for (int m = 0; m < 4; ++m) r[m] = -s[m];
+        slash_col_add(e[c], W[b], r);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) A[t][2 * a + 1] = sdot_add(U[t], r, c64{0.0, 0.0});
+      }
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const int a = c == 0 ? 1 : 0, b = c == 2 ? 1 : 2;
+        slash_col(J[c], W[c], s);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const c64 x = sdot_add(u[t], s, c64{0.0, 0.0});
+          A[t][2 * a + (b > c)] = A[t][2 * a + (b > c)] + x;
+          A[t][2 * b + (a > c)] = A[t][2 * b + (a > c)] - x;
+        }
+      }
+      c64 y[2][2];
+#pragma unroll
+      for (int m = 0; m < 2; ++m) {
+        slash_col(M[m], v[tb], s);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) y[t][m] = sdot_add(u[t], s, c64{0.0, 0.0});
+      }
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const c64 y2 = -(y[t][0] + y[t][1]);
+        A[t][0] = A[t][0] + y[t][1];  // (012)
+        A[t][5] = A[t][5] + y[t][1];  // (210)
+        A[t][2] = A[t][2] + y[t][0];  // (102)
+        A[t][4] = A[t][4] + y[t][0];  // (201)
+        A[t][1] = A[t][1] + y2;       // (021)
+        A[t][3] = A[t][3] + y2;       // (120)
+        emit(t, tb, cp.gs2 * Sum::sum(A[t]));
+      }
+    };
+    of_antiquark(0);
+    of_antiquark(1);
+  }
+};
+
+// e+ e- -> mu+ mu-: massless leptons have one current per chirality and side,
+//   j(L) = chi-^+(f) sbar^mu chi-(g),  j(R) = chi+^+(f) s^mu chi+(g)
+// (times sqrt(E + P) of both), f the row (e+, mu-), g the column (e-, mu+),
+// and four of the 16 helicities; the others vanish identically.
+struct LeptonCurrents {
+  c64 j[2][4];  // chirality L, R
+};
+template <int AF, int AG>
+__device__ __forceinline__ void lepton_currents(const double (&pf)[4], const double (&pg)[4],
+                                                LeptonCurrents& o) {
+  double fc, fx, fy, fb, gc, gx, gy, gb, none;
+  helicity_states<AF>(pf, 0.0, fc, fx, fy, fb, none);
+  helicity_states<AG>(pg, 0.0, gc, gx, gy, gb, none);
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const c64 f0 = h ? c64{fc, 0.0} : c64{-fx, -fy}, f1 = h ? c64{fx, -fy} : c64{fc, 0.0};
+    const c64 g0 = gb * fb * (h ? c64{gc, 0.0} : c64{-gx, gy}),
+              g1 = gb * fb * (h ? c64{gx, gy} : c64{gc, 0.0});
+    const c64 a00 = f0 * g0, a11 = f1 * g1, a01 = f0 * g1, a10 = f1 * g0;
+    const double s = h ? 1.0 : -1.0;
+    o.j[h][0] = a00 + a11;
+    o.j[h][1] = s * (a01 + a10);
+    o.j[h][2] = s * times_i(a10 - a01);
+    o.j[h][3] = s * (a00 - a11);
+  }
+}
+
+template <class P, bool BEAM, class Take>
+__device__ __forceinline__ void eemumu_shared(const double (&p)[4][4], const Couplings<double>& c,
+                                              Take take) {
+  LeptonCurrents e, mu;
+  lepton_currents<BEAM ? 1 : 0, BEAM ? -1 : 0>(p[0], p[1], e);
+  lepton_currents<0, 0>(p[3], p[2], mu);
+  double K[4];
+  plus4(p[0], p[1], K);
+  const double k2 = msq(K), re = k2 - c.mz * c.mz, im = c.mz * c.wz;
+  const double photon = c.cqed * c.cqed * recip(k2);
+  const double n = recip(re * re + im * im);
+  const c64 d{re * n, -im * n};
+  const double im2 = recip(c.mz * c.mz);
+  c64 ke[2], km[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    ke[h] = im2 * mdot(K, e.j[h]);
+    km[h] = mdot(K, mu.j[h]);
+  }
+#pragma unroll
+  for (int h = 0; h < 16; ++h) {
+    // e+ and e-, mu+ and mu- have opposite helicities; L: the first of each +
+    const int a = (h >> 2) == 1 ? 1 : 0, b = (h & 3) == 1 ? 1 : 0;
+    double v = 0.0;
+    if (((h >> 2) == 1 || (h >> 2) == 2) && ((h & 3) == 1 || (h & 3) == 2)) {
+      const double zz = (a ? c.czr : c.czl) * (b ? c.czr : c.czl);
+      const c64 s = mdot0(e.j[a], mu.j[b]);
+      const c64 A = photon * s + zz * (d * (s - ke[a] * km[b]));
+      v = A.r * A.r + A.i * A.i;
+    }
+    take(h, v);
+  }
+}
+
+// The colour sum of a process for the objects above
+template <class P>
+struct ColourSum {
+  __device__ static __forceinline__ double sum(const c64 (&A)[P::NCOL]) {
+    return P::template colour_sum<double>(A);
+  }
+};
+
+// One event per lane: |M|^2 summed over the helicities of hel_mask
+template <class P, int BS>
+__global__ void __launch_bounds__(BS, 2)
+    sigmakin_shared_kernel(const double* __restrict__ mom, int64_t nevt, double* __restrict__ me,
+                           const double* __restrict__ wgt, double* __restrict__ evtw,
+                           double* __restrict__ mehel, uint64_t hel_mask, Couplings<double> c,
+                           double inv_iden) {
+  const int64_t i = (int64_t)blockIdx.x * BS + threadIdx.x;
+  if (i >= nevt) return;
+  double p[P::NPAR][4];
+  load_event<P>(mom, i, p);
+  double acc = 0.0;
+  auto take = [&](int h, double v) {
+    if (mehel) mehel[(int64_t)h * nevt + i] = v;
+    acc += (hel_mask >> h) & 1 ? v : 0.0;
+  };
+  if (__all(beams_on_axis(p))) {
+    set_beams(p);
+    P::template shared<true>(p, c, take);
+  } else {
+    P::template shared<false>(p, c, take);
+  }
+  const double m = acc * inv_iden;
+  if (me) me[i] = m;
+  if (evtw) evtw[i] = m * wgt[i];
+}
+
+// all helicities of one event in a lane
+template <class P, bool BEAM, class Take>
+__device__ __forceinline__ void ggtt_shared(const double (&p)[4][4], const Couplings<double>& c,
+                                            Take take) {
+  GGTT<BEAM, ColourSum<P>> ev(p, c);
+#pragma unroll
+  for (int h = 0; h < 4; ++h)
+    ev.flows_sum(h & 2 ? 1 : -1, h & 1 ? 1 : -1,
+                 [&](int t, int tb, double v) { take((h << 2) | (t << 1) | tb, v); });
+}
+
+// Eight lanes per event, one for each helicity of the three gluons, each with
+// the four quark helicities; the sum over the lanes is a DPP butterfly.  The
+// t-side spinors U(a) wait in LDS (24 KB a wave): in registers they cost
+// 608 bytes of scratch a lane and 11 % more time.
+template <class P>
+__global__ void __launch_bounds__(64)
+    sigmakin_gluon_lanes_kernel(const double* __restrict__ mom, int64_t nevt,
+                                double* __restrict__ me, const double* __restrict__ wgt,
+                                double* __restrict__ evtw, double* __restrict__ mehel,
+                                uint64_t hel_mask, Couplings<double> c, double inv_iden) {
+  const int64_t j = (int64_t)blockIdx.x * 64 + threadIdx.x;
+  const int64_t i = j >> 3;
+  if (i >= nevt) return;
+  const int g = (int)j & 7;
+  __shared__ d2 lds[6 * 256];
+  d2* park = lds + threadIdx.x;
+  double p[P::NPAR][4];
+  load_event<P>(mom, i, p);
+  double acc = 0.0;
+  const int code = ((g & 6) << 2) | (g & 1);  // gluons 0 and 1: bits 4, 3; gluon 2: bit 0
+  auto take = [&](int t, int tb, double v) {
+    const int h = code | (t << 2) | (tb << 1);
+    if (mehel) mehel[(int64_t)h * nevt + i] = v;
+    acc += (hel_mask >> h) & 1 ? v : 0.0;
+  };
+  const int l0 = g & 4 ? 1 : -1, l1 = g & 2 ? 1 : -1, l2 = g & 1 ? 1 : -1;
+  if (__all(beams_on_axis(p))) {
+    set_beams(p);
+    GGTTG<true, ColourSum<P>>(p, c).flows_sum(l0, l1, l2, park, take);
+  } else {
+    GGTTG<false, ColourSum<P>>(p, c).flows_sum(l0, l1, l2, park, take);
+  }
+  acc += dpp_move<0xB1>(acc);   // quad_perm 1 0 3 2
+  acc += dpp_move<0x4E>(acc);   // quad_perm 2 3 0 1
+  acc += dpp_move<0x141>(acc);  // row_half_mirror
+  if (g == 0) {
+    const double m = acc * inv_iden;
+    if (me) me[i] = m;
+    if (evtw) evtw[i] = m * wgt[i];
+  }
+}
+
+inline uint64_t helicity_mask(const HelList& l) {
+  uint64_t m = 0;
+  for (int k = 0; k < l.n; ++k) m |= 1ull << l.code[k];
+  return m;
+}
+
+template <class P, int BS>
+int sigmakin_shared_launch(const MeArgs& a, const double* mom, int64_t nevt, double* me,
+                           const double* wgt, double* evtw, double* mehel, hipStream_t s) {
+  const unsigned g = (unsigned)((nevt + BS - 1) / BS);
+  sigmakin_shared_kernel<P, BS><<<g, BS, 0, s>>>(mom, nevt, me, wgt, evtw, mehel,
+                                                 helicity_mask(a.hel), a.c64, a.inv_iden);
+  return 0;
+}
+
 template <class P>
 int sigmakin_ggttgg_shared_launch(const MeArgs& a, const double* mom, int64_t nevt, double* me,
                                   const double* wgt, double* evtw, double* mehel, hipStream_t s) {
-  uint64_t mask = 0;
-  for (int k = 0; k < a.hel.n; ++k) mask |= 1ull << a.hel.code[k];
   sigmakin_ggttgg_shared_kernel<P><<<(unsigned)nevt, 64, 0, s>>>(mom, nevt, me, wgt, evtw, mehel,
-                                                                mask, a.c64, a.inv_iden);
+                                                                helicity_mask(a.hel), a.c64, a.inv_iden);
   return 0;
 }
 

@@ -262,23 +262,44 @@ __global__ void __launch_bounds__(BS)
 }
 
 // the group kernel when the kept helicities are a power of two and the
-// launch has fewer than `max_events` events (where the event-per-lane kernel
-// leaves compute units idle), else the event-per-lane kernel
+// launch has fewer than `max_events` events (where the other kernels leave
+// compute units idle); false: not launched
+template <class P, typename T, int BS>
+bool sigmakin_group_taken(const MeArgs& a, const Couplings<T>& c, const double* mom, int64_t nevt,
+                          double* me, const double* wgt, double* evtw, double* mehel,
+                          int64_t max_events, hipStream_t s) {
+  const int n = a.hel.n;
+  if (mehel || nevt <= 0 || nevt >= max_events || n < 2 || n > 64 || (n & (n - 1)) != 0)
+    return false;
+  int lg = 0;
+  while ((1 << lg) < n) ++lg;
+  const int64_t threads = nevt << lg;
+  const unsigned g = (unsigned)((threads + BS - 1) / BS);
+  sigmakin_group_kernel<P, T, BS><<<g, BS, 0, s>>>(mom, nevt, me, wgt, evtw, a.hel, c, a.inv_iden,
+                                                   lg);
+  return true;
+}
+
 template <class P, typename T, int BS>
 int sigmakin_group_launch(const MeArgs& a, const Couplings<T>& c, const double* mom, int64_t nevt,
                           double* me, const double* wgt, double* evtw, double* mehel,
                           int64_t max_events, hipStream_t s) {
-  const int n = a.hel.n;
-  if (!mehel && nevt > 0 && nevt < max_events && n > 1 && n <= 64 && (n & (n - 1)) == 0) {
-    int lg = 0;
-    while ((1 << lg) < n) ++lg;
-    const int64_t threads = nevt << lg;
-    const unsigned g = (unsigned)((threads + BS - 1) / BS);
-    sigmakin_group_kernel<P, T, BS><<<g, BS, 0, s>>>(mom, nevt, me, wgt, evtw, a.hel, c,
-                                                     a.inv_iden, lg);
-    return 0;
-  }
+  if (sigmakin_group_taken<P, T, BS>(a, c, mom, nevt, me, wgt, evtw, mehel, max_events, s)) return 0;
   return sigmakin_launch<P, T, BS>(a, c, mom, nevt, me, wgt, evtw, mehel, s);
+}
+
+// FP64 g g -> t t~ g: the group kernel, else a lane per gluon helicity
+template <class P>
+int sigmakin_gluon_lanes_launch(const MeArgs& a, const double* mom, int64_t nevt, double* me,
+                                const double* wgt, double* evtw, double* mehel,
+                                int64_t max_group, hipStream_t s) {
+  if (sigmakin_group_taken<P, double, MG_EPL_BLOCK>(a, a.c64, mom, nevt, me, wgt, evtw, mehel,
+                                                    max_group, s))
+    return 0;
+  const unsigned g = (unsigned)((nevt + 7) / 8);
+  sigmakin_gluon_lanes_kernel<P><<<g, 64, 0, s>>>(mom, nevt, me, wgt, evtw, mehel,
+                                                  helicity_mask(a.hel), a.c64, a.inv_iden);
+  return 0;
 }
 
 // Matrix-core colour sum of one helicity per lane.  The amplitudes reach it

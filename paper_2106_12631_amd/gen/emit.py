@@ -1087,6 +1087,11 @@ HPL_PROCESSES = ('ggttgg',)
 # at 4096-16384 events, 1.22x at 2^15, 0.94x at 2^16, 0.77x at 2^20;
 # g g -> t t~ 4.0x at 4096, 1.55x at 2^15, 0.96x at 2^16; g g -> t t~ g 8.0x
 # at 4096, 1.36x at 2^15, 0.77x at 2^16)
+# FP64 shares the currents between helicities instead (shared_currents.h) and
+# wins at every size, except for g g -> t t~ g below GROUP_MAX_EVENTS_F64: the
+# group kernel takes 7.2 us up to 2048 events (one wave per SIMD) and 12.6 us
+# above, the shared one 8.1 us there and 8.3 us at 4096 events.
+GROUP_MAX_EVENTS_F64 = {'ggttg': 2049}
 GROUP_MAX_EVENTS = {'eemumu': 1 << 16, 'ggtt': 1 << 16, 'ggttg': 1 << 16}
 # Processes whose event-per-lane kernels re-read the momenta for every
 # helicity (REREAD_MOMENTA, sigmakin_impl.h): those whose amplitude code
@@ -1129,7 +1134,12 @@ def emit_units(name):
 ''' + (f'''  __device__ static __forceinline__ double colour_sum_blocks(cx<double> (&J)[NCOL]) {{
     return gen_{name}::colour_sum_blocks(J);
   }}
-''' if hpl else '') + '''};
+''' if hpl else f'''  template <bool BEAM, class Take>
+  __device__ static __forceinline__ void shared(const double (&p)[NPAR][4], const Couplings<double>& c,
+                                                Take take) {{
+    {name}_shared<P_{name}, BEAM>(p, c, take);
+  }}
+''' if name != 'ggttg' else '') + '''};
 '''
     sk_args = '(const MeArgs& a, const double* mom, int64_t nevt, double* me, const double* wgt,\n' \
               '    double* evtw, double* mehel, hipStream_t s)'
@@ -1144,6 +1154,12 @@ def emit_units(name):
                        if prec == 'f64' else
                        f'  return sigmakin_hpl_launch<P_{name}, {T}, 64>(a, a.{c}, mom, nevt, me, wgt, evtw, mehel, s);\n') +
                     f'#endif\n')
+        elif prec == 'f64' and name == 'ggttg':
+            body = (f'  return sigmakin_gluon_lanes_launch<P_{name}>(a, mom, nevt, me, wgt, evtw, mehel,\n'
+                    f'      group_max_events({GROUP_MAX_EVENTS_F64[name]}), s);\n')
+        elif prec == 'f64':
+            body = (f'  return sigmakin_shared_launch<P_{name}, MG_EPL_BLOCK>(a, mom, nevt, me, wgt, evtw,\n'
+                    f'      mehel, s);\n')
         else:
             body = f'  return {epl};\n'
         src = head.format(what=f'{T} amplitudes') + '#include "sigmakin_impl.h"\n\nnamespace mg {\n' \

@@ -1,7 +1,8 @@
 """The FP64 kernels whose currents are shared between helicities (GPU).
 
 Sizes at the edges of the event-to-wave mapping (one event, fewer events
-than XCDs, a page and a page plus one), incoming momenta on the axis and
+than XCDs, a page and a page plus one; g g -> t t~ g above the size up to
+which it spreads helicities over lanes), incoming momenta on the axis and
 after a rotation and a boost, every helicity by itself, massless quarks
 (half of the helicities exactly zero and filtered out), and the zero-width
 flag, against the oracle on the oracle's momenta.
@@ -23,7 +24,7 @@ from rounding import EPS, invariant_condition
 
 pytestmark = pytest.mark.gpu
 
-PROCS = ('ggttgg',)
+PROCS = ('eemumu', 'ggtt', 'ggttg', 'ggttgg')
 SIZES = (1, 7, 64, 65, 129)
 
 
@@ -62,8 +63,7 @@ def compare(eng, proc, p, prm):
     return got
 
 
-@pytest.mark.parametrize('proc', PROCS)
-@pytest.mark.parametrize('n', SIZES)
+@pytest.mark.parametrize('proc,n', [(p, n) for p in PROCS for n in SIZES] + [('ggttg', 2113)])
 def test_sizes_and_frames(mg, proc, n):
     eng = mg.MEEngine(proc, 'fp64')
     _, p, _ = orc.sample(proc, 21, 0, n)
@@ -73,7 +73,7 @@ def test_sizes_and_frames(mg, proc, n):
     compare(eng, proc, moved(p), DEFAULT)
 
 
-@pytest.mark.parametrize('proc', PROCS)
+@pytest.mark.parametrize('proc', PROCS[1:])
 def test_massless_quarks_and_zero_width(mg, proc):
     n = 65
     prm = DEFAULT.with_(mt=0.0, wt=0.0)
