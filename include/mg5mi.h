@@ -190,7 +190,9 @@ int mg_sigmakin_hel(const mg_handle_t* h, const double* mom, int64_t nevt, doubl
  * final-state momenta; the RAMBO Jacobian (including the Newton rescaling,
  * by the implicit-function theorem) comes from one dual-number pass per
  * uniform.  FP64 for MG_FP64, FP32 amplitudes and adjoints with FP64 RAMBO,
- * momentum adjoints and sums otherwise.  Built for e+e- -> mu+mu-, g g -> t t~ and
+ * momentum adjoints and sums otherwise.  FP64 g g -> t t~ and g g -> t t~ g
+ * use the events' slots of grad_rnd as scratch (three kernels; grad_rnd may
+ * still be rnd itself, at the cost of a slower kernel).  Built for e+e- -> mu+mu-, g g -> t t~ and
  * g g -> t t~ g; MG_ENOTSUP for g g -> t t~ g g. */
 int mg_adjoint(const mg_handle_t* h, const double* rnd, int64_t nevt, const double* gbar_or_null,
                double* grad_rnd, double* grad_logw_or_null, double* f_or_null, void* stream);

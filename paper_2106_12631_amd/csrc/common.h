@@ -72,4 +72,25 @@ struct Beam {
   static constexpr bool value = B;
 };
 
+// Workgroups are handed to the 8 XCDs of the chip in turn (block b to XCD
+// b % 8), each with its own L2.  With one event per block, consecutive
+// events share the 64-byte lines of the AoSoA momenta, so the event of
+// block b is chosen to give XCD x one contiguous range of events, walked in
+// dispatch order: a bijection of [0, nblocks).
+__device__ __forceinline__ int64_t xcd_event(int64_t b, int64_t nblocks) {
+  constexpr int NXCD = 8;
+  const int64_t q = nblocks / NXCD, r = nblocks % NXCD;
+  const int64_t x = b % NXCD, k = b / NXCD;
+  return x * q + (x < r ? x : r) + k;
+}
+
+template <class P>
+__device__ __forceinline__ void load_event(const double* __restrict__ mom, int64_t i,
+                                           double (&p)[P::NPAR][4]) {
+#pragma unroll
+  for (int ip = 0; ip < P::NPAR; ++ip)
+#pragma unroll
+    for (int m = 0; m < 4; ++m) p[ip][m] = mom[aosoa_mom(i, ip, m, P::NPAR)];
+}
+
 }  // namespace mg

@@ -22,6 +22,13 @@ int launch_rambo(int nf, const double* rnd, int64_t nevt, const RamboArgs& a, do
 int launch_sample(int nf, uint64_t seed, int64_t off, int64_t nevt, const RamboArgs& a,
                   double* rnd, double* mom, double* wgt, hipStream_t s);
 
+// first and last kernel of the shared-current gradient (rambo_grad.hip)
+int launch_grad_momenta(int nf, const double* rnd, int64_t nevt, const RamboArgs& a, double* buf,
+                        hipStream_t s);
+int launch_grad_uniforms(int nf, const double* rnd, int64_t nevt, const RamboArgs& a,
+                         double inv_iden, const double* gbar, double* grad, double* logw,
+                         double* f, hipStream_t s);
+
 struct MeArgs {
   Couplings<double> c64;
   Couplings<float> c32;

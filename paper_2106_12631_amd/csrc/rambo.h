@@ -45,6 +45,31 @@ __device__ __forceinline__ double failed_weight() {
   return __builtin_bit_cast(double, bits);
 }
 
+// Newton solve of sum_i sqrt(m_i^2 + xi^2 E_i^2) = sqrt(s) for the common
+// scale xi of the three-momenta; ok: converged
+template <int NF>
+__device__ __forceinline__ double rambo_scale(const double (&E)[NF], const RamboArgs& a,
+                                              bool& ok) {
+  double xiv = a.xi0;
+  ok = false;
+  for (int it = 0; it <= 50; ++it) {
+    double f = -a.sqrts, fp = 0.0;
+#pragma unroll
+    for (int i = 0; i < NF; ++i) {
+      const double root = sqrt(a.m2[i] + xiv * xiv * E[i] * E[i]);
+      f += root;
+      fp += xiv * E[i] * E[i] / root;
+    }
+    if (fabs(f) <= 1e-14 * a.sqrts) {
+      ok = true;
+      break;
+    }
+    if (it == 50) break;
+    xiv -= f / fp;
+  }
+  return xiv;
+}
+
 // p[0], p[1] are the incoming momenta along +z and -z; returns false (and a
 // NaN weight) if the Newton solve did not converge.
 template <int NF, typename R>
@@ -102,25 +127,11 @@ __device__ __forceinline__ bool rambo(const R (&r)[4 * NF], const RamboArgs& a,
   }
   w = a.w0;
   if (!a.massive) return true;
-  // Newton solve of sum_i sqrt(m_i^2 + xi^2 E_i^2) = sqrt(s) on the values
-  double xiv = a.xi0;
-  bool ok = false;
-  for (int it = 0; it <= 50; ++it) {
-    double f = -a.sqrts, fp = 0.0;
+  double Ev[NF];
 #pragma unroll
-    for (int i = 0; i < NF; ++i) {
-      const double E = val(p[i + 2][0]);
-      const double root = sqrt(a.m2[i] + xiv * xiv * E * E);
-      f += root;
-      fp += xiv * E * E / root;
-    }
-    if (fabs(f) <= 1e-14 * a.sqrts) {
-      ok = true;
-      break;
-    }
-    if (it == 50) break;
-    xiv -= f / fp;
-  }
+  for (int i = 0; i < NF; ++i) Ev[i] = val(p[i + 2][0]);
+  bool ok;
+  const double xiv = rambo_scale<NF>(Ev, a, ok);
   R E[NF];
 #pragma unroll
   for (int i = 0; i < NF; ++i) E[i] = p[i + 2][0];

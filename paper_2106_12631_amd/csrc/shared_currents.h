@@ -25,6 +25,7 @@
 // run through the same code.
 #pragma once
 #include "common.h"
+#include "internal.h"
 
 namespace mg {
 
@@ -927,11 +928,9 @@ struct GGTTG {
     }
   }
 
-  // park: this lane's slots for U(a), component k of slot s at [256 s + 64 k].
-  // A(abc) / g = U(a).(b-slash W(c) + J-slash(bc) v) + u.(J-slash(ab) W(c) + J-slash(abc) v)
-  template <class Emit>
-  __device__ __forceinline__ void flows_sum(int lam0, int lam1, int lam2, d2* park, Emit emit) {
-    c64 e[3][4], J[3][4], M[2][4];  // J[c]: the pair without c; M[m]: J(x m y), m in the middle
+  // polarisation vectors, J[c]: the pair without c, M[m]: J(x m y), m in the middle
+  __device__ __forceinline__ void gluon_currents(int lam0, int lam1, int lam2, c64 (&e)[3][4],
+                                                 c64 (&J)[3][4], c64 (&M)[2][4]) {
     polarisation<BEAM ? 1 : 0>(k[0], lam0, false, e[0]);
     polarisation<BEAM ? -1 : 0>(k[1], lam1, false, e[1]);
     {
@@ -966,6 +965,14 @@ struct GGTTG {
                                cmsub(e[0][m], d12, cmsub(e[2][m], d01, -(L1[m] + L2[m]))));
       }
     }
+  }
+
+  // park: this lane's slots for U(a), component k of slot s at [256 s + 64 k].
+  // A(abc) / g = U(a).(b-slash W(c) + J-slash(bc) v) + u.(J-slash(ab) W(c) + J-slash(abc) v)
+  template <class Emit>
+  __device__ __forceinline__ void flows_sum(int lam0, int lam1, int lam2, d2* park, Emit emit) {
+    c64 e[3][4], J[3][4], M[2][4];
+    gluon_currents(lam0, lam1, lam2, e, J, M);
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll

@@ -1077,6 +1077,9 @@ def generate(name, orders=None):
     return "\n".join(L) + "\n", meta
 
 
+# Processes whose FP64 gradient shares the currents between helicities
+# (shared_adjoint.h).
+GRAD_SHARED = {'ggtt': 'GradGGTT', 'ggttg': 'GradGGTTG'}
 # One event per wave and one helicity per lane: the processes whose 64
 # helicities fill a wave64 (all kept at the benchmark parameters).
 HPL_PROCESSES = ('ggttgg',)
@@ -1214,11 +1217,31 @@ struct {prec.upper()}_{name} {{
   }}
 }};
 '''
+        fp64 = '  if (prec == 0)\n'
+        if name in GRAD_SHARED:
+            src = src.replace('#include "adjoint_impl.h"\n', '#include "adjoint_impl.h"\n#include "shared_adjoint.h"\n')
+            src += f'''
+struct S_{name} {{
+  static constexpr int NPAR = gen_{name}::NPAR;
+  static constexpr int NCOL = gen_{name}::NCOL;
+  static constexpr int CDEN = gen_{name}::CDEN;
+  __device__ static constexpr int cnum(int i, int j) {{ return gen_{name}::CNUM[i][j]; }}
+  template <typename T>
+  __device__ static __forceinline__ T colour_sum(const cx<T> (&J)[NCOL]) {{
+    return gen_{name}::colour_sum<T>(J);
+  }}
+}};
+'''
+            fp64 = (f'  // the shared-current gradient works in the gradient buffer: not when it is an\n'
+                    f'  // input too\n'
+                    f'  if (prec == 0 && !grad_in_place(rnd, gbar, grad_rnd, nevt, {4 * nf}))\n'
+                    f'    return shared_gradient_launch<S_{name}, {GRAD_SHARED[name]}<S_{name}>>(\n'
+                    f'        a, ra, rnd, nevt, gbar, grad_rnd, grad_logw, mew, s);\n') + fp64
         src += f'''
 int launch_grad_{name}(int prec, const MeArgs& a, const RamboArgs& ra, const double* rnd,
     int64_t nevt, const double* gbar, double* grad_rnd, double* grad_logw, double* mew,
     hipStream_t s) {{
-  if (prec == 0)
+{fp64}''' + f'''\
     return adjoint_launch<A64_{name}, {nf}, double>(a, ra, a.c64, rnd, nevt, gbar, grad_rnd,
                                                    grad_logw, mew, s);
   return adjoint_launch<A32_{name}, {nf}, float>(a, ra, a.c32, rnd, nevt, gbar, grad_rnd,
