@@ -683,6 +683,15 @@ __device__ __forceinline__ void flows(const double* __restrict__ mom, int64_t i,
   }
 }
 
+// |M|^2 summed over colours for the helicity code of the lane
+template <class P>
+__device__ __forceinline__ double hel_value(const double* __restrict__ mom, int64_t i,
+                                            const Couplings<double>& c, d2* lds, int lane) {
+  c64 A[P::NCOL];
+  flows<P>(mom, i, c, lds, lane, A);
+  return c.gs2 * P::colour_sum_blocks(A);
+}
+
 }  // namespace ggttgg_shared
 
 // One event per wave, lane h assembling helicity h from the shared currents.
@@ -696,9 +705,7 @@ __global__ void __launch_bounds__(64, 2)
   __shared__ d2 lds[ggttgg_shared::LDS_UNITS];
   const int64_t i = xcd_event(blockIdx.x, nevt);
   const int lane = threadIdx.x;
-  c64 A[P::NCOL];
-  ggttgg_shared::flows<P>(mom, i, c, lds, lane, A);
-  double v = c.gs2 * P::colour_sum_blocks(A);
+  double v = ggttgg_shared::hel_value<P>(mom, i, c, lds, lane);
   if (mehel) mehel[(int64_t)lane * nevt + i] = v;
   v = wave_sum((hel_mask >> lane) & 1 ? v : 0.0);
   if (lane == 0) {

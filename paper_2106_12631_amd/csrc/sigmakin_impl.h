@@ -360,6 +360,19 @@ __device__ __forceinline__ bool ill_conditioned(const double (&p)[NPAR][4], doub
   return E * E - X * X - Y * Y - Z * Z > kmax * m;
 }
 
+// the events of the wave's page that need it, one bit each
+template <class P>
+__device__ __forceinline__ uint64_t guard_scan(const double* __restrict__ mom, int64_t i,
+                                               int64_t nevt, double kmax) {
+  bool flag = false;
+  if (i < nevt) {
+    double q[P::NPAR][4];
+    load_event<P>(mom, i, q);
+    flag = ill_conditioned<P::NPAR>(q, kmax);
+  }
+  return __ballot(flag);
+}
+
 template <class P>
 __global__ void __launch_bounds__(64)
     sigmakin_guard_kernel(const double* __restrict__ mom, int64_t nevt, double* __restrict__ me,
@@ -367,13 +380,7 @@ __global__ void __launch_bounds__(64)
                           Couplings<double> c, double inv_iden, double kmax) {
   const int lane = threadIdx.x;
   const int64_t i0 = (int64_t)blockIdx.x * 64;
-  bool flag = false;
-  if (i0 + lane < nevt) {
-    double q[P::NPAR][4];
-    load_event<P>(mom, i0 + lane, q);
-    flag = ill_conditioned<P::NPAR>(q, kmax);
-  }
-  uint64_t pending = __ballot(flag);
+  uint64_t pending = guard_scan<P>(mom, i0 + lane, nevt, kmax);
   while (pending) {
     const int l = __ffsll((unsigned long long)pending) - 1;
     pending &= pending - 1;
@@ -394,6 +401,42 @@ __global__ void __launch_bounds__(64)
       if (evtw) evtw[e] = m * wgt[e];
     }
   }
+}
+
+// the same for g g -> t t~ g g with the shared currents of a wave (at two
+// waves per SIMD and a fifth of the work per event: 2^19 events in 70 us
+// instead of 164)
+template <class P>
+__global__ void __launch_bounds__(64, 2)
+    sigmakin_guard_shared_kernel(const double* __restrict__ mom, int64_t nevt,
+                                 double* __restrict__ me, const double* __restrict__ wgt,
+                                 double* __restrict__ evtw, uint64_t hel_mask, Couplings<double> c,
+                                 double inv_iden, double kmax) {
+  __shared__ d2 lds[ggttgg_shared::LDS_UNITS];
+  const int lane = threadIdx.x;
+  const int64_t i0 = (int64_t)blockIdx.x * 64;
+  uint64_t pending = guard_scan<P>(mom, i0 + lane, nevt, kmax);
+  while (pending) {
+    const int64_t e = i0 + __ffsll((unsigned long long)pending) - 1;
+    pending &= pending - 1;
+    const double v = ggttgg_shared::hel_value<P>(mom, e, c, lds, lane);
+    const double m = wave_sum((hel_mask >> lane) & 1 ? v : 0.0) * inv_iden;
+    if (lane == 0) {
+      me[e] = m;
+      if (evtw) evtw[e] = m * wgt[e];
+    }
+    __syncthreads();
+  }
+}
+
+template <class P>
+int sigmakin_guard_shared_launch(const MeArgs& a, const double* mom, int64_t nevt, double* me,
+                                 const double* wgt, double* evtw, hipStream_t s) {
+  if (!(a.guard_kappa > 0.0) || nevt <= 0) return 0;
+  const unsigned g = (unsigned)((nevt + 63) / 64);
+  sigmakin_guard_shared_kernel<P><<<g, 64, 0, s>>>(mom, nevt, me, wgt, evtw, helicity_mask(a.hel),
+                                                   a.c64, a.inv_iden, a.guard_kappa);
+  return 0;
 }
 
 template <class P>

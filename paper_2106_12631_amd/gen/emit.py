@@ -1174,7 +1174,7 @@ def emit_units(name):
                     f'// launch (precision guard of sigmakin_impl.h)\n'
                     f'int launch_sigmakin_{name}_guard(const MeArgs& a, const double* mom, int64_t nevt,\n'
                     f'    double* me, const double* wgt, double* evtw, hipStream_t s) {{\n'
-                    f'  return sigmakin_guard_launch<P_{name}>(a, mom, nevt, me, wgt, evtw, s);\n}}\n')
+                    f'  return sigmakin_guard_{"shared_" if hpl else ""}launch<P_{name}>(a, mom, nevt, me, wgt, evtw, s);\n}}\n')
         units[f'sigmakin_{name}_{prec}.hip'] = src + '\n}  // namespace mg\n'
     # mixed: event-per-lane body for the matrix-core colour sum (jamps_f32m)
     # and, for the helicity-per-lane processes, the FP32 body of that kernel
