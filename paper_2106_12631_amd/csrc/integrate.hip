@@ -12,8 +12,8 @@
 // Philox uniform of (seed, event evt_offset + i) at block UNW_BLOCK (a
 // counter block no sampler uses, so the same seed may serve both).  The
 // kept indices are written in increasing order (stream compaction):
-//   unw_count_kernel   per 256-event block: number kept -> ws[b]
-//   unw_scan_kernel    one block: exclusive prefix sum of ws in place, total
+//   unw_count_kernel   per block of R groups of 256 events: number kept -> ws
+//   unw_scan_kernel    one block: exclusive prefix sum in place, total
 //   unw_write_kernel   per block: wave ballots + LDS offsets -> idx_out
 #include <mutex>
 
@@ -107,66 +107,118 @@ __global__ void __launch_bounds__(1024) xsec_final_kernel(const double* __restri
   if (t < 4) out[t] = s[t][0];
 }
 
-__device__ __forceinline__ bool keep(const double* f, int64_t i, int64_t n, double fmax,
-                                     uint64_t seed, int64_t off) {
-  if (i >= n) return false;
-  const double v = f[i];
+// f of event i, NaN (never kept) past the end
+__device__ __forceinline__ double weight_at(const double* f, int64_t i, int64_t n) {
+  return i < n ? f[i] : __builtin_nan("");
+}
+__device__ __forceinline__ bool keep(double v, int64_t i, double fmax, uint64_t seed, int64_t off) {
   return unweight_uniform(seed, (uint64_t)(off + i)) * fmax < v;  // false for NaN
 }
 
+// Block b of 256 threads takes the R groups of 256 events from 256 R b on, in
+// chunks of 64 (one ballot each): chunk 4 q + w of group q to wave w.  Its kept
+// events go to ws[R b], and which of its 4 R chunks keep any, one bit each, to
+// ws[R b + 1] where the workspace (a word per group) has that word.
+template <int R>
 __global__ void __launch_bounds__(256) unw_count_kernel(const double* __restrict__ f, int64_t n,
                                                         double fmax, uint64_t seed, int64_t off,
-                                                        int64_t* __restrict__ ws) {
+                                                        int64_t slots, int64_t* __restrict__ ws) {
   __shared__ int cnt[4];
+  __shared__ uint64_t any[4];
   const int t = threadIdx.x, w = t >> 6;
-  const int64_t i = (int64_t)blockIdx.x * 256 + t;
-  const uint64_t m = __ballot(keep(f, i, n, fmax, seed, off));
-  if ((t & 63) == 0) cnt[w] = __popcll(m);
+  const int64_t i0 = (int64_t)blockIdx.x * (256 * R) + t;
+  int c = 0;
+  uint64_t bits = 0;
+  double v[R];  // all loads in flight at once
+#pragma unroll
+  for (int q = 0; q < R; ++q) v[q] = weight_at(f, i0 + 256 * q, n);
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const uint64_t m = __ballot(keep(v[q], i0 + 256 * q, fmax, seed, off));
+    c += __popcll(m);
+    bits |= (uint64_t)(m != 0) << (4 * q + w);
+  }
+  if ((t & 63) == 0) {
+    cnt[w] = c;
+    any[w] = bits;
+  }
   __syncthreads();
-  if (t == 0) ws[blockIdx.x] = cnt[0] + cnt[1] + cnt[2] + cnt[3];
+  const int64_t k = (int64_t)blockIdx.x * R;
+  if (t == 0) ws[k] = cnt[0] + cnt[1] + cnt[2] + cnt[3];
+  if (R > 1 && t == 1 && k + 1 < slots) ws[k + 1] = (int64_t)(any[0] | any[1] | any[2] | any[3]);
 }
 
-// exclusive scan of ws[0..nb) in place; total -> *count
+// inclusive sum over the lanes of a wave up to this one
+__device__ __forceinline__ int64_t wave_prefix(int64_t v, int lane) {
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int64_t o = __shfl_up(v, d);
+    v += lane >= d ? o : 0;
+  }
+  return v;
+}
+
+// exclusive scan of the nb counts ws[0], ws[stride], ... in place; total -> *count
 __global__ void __launch_bounds__(1024) unw_scan_kernel(int64_t* __restrict__ ws, int64_t nb,
+                                                        int64_t stride,
                                                         int64_t* __restrict__ count) {
-  __shared__ int64_t part[1024];
-  const int t = threadIdx.x;
+  __shared__ int64_t part[16];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int64_t chunk = (nb + 1023) / 1024;
   const int64_t b = (int64_t)t * chunk, e = b + chunk < nb ? b + chunk : nb;
   int64_t s = 0;
-  for (int64_t k = b; k < e; ++k) s += ws[k];
-  part[t] = s;
+  for (int64_t k = b; k < e; ++k) s += ws[k * stride];
+  const int64_t incl = wave_prefix(s, lane);
+  if (lane == 63) part[w] = incl;
   __syncthreads();
-  // Hillis-Steele inclusive scan over the 1024 partial sums
-  for (int d = 1; d < 1024; d <<= 1) {
-    const int64_t add = t >= d ? part[t - d] : 0;
-    __syncthreads();
-    part[t] += add;
-    __syncthreads();
-  }
-  int64_t run = t ? part[t - 1] : 0;
+  int64_t run = incl - s;
+  for (int v = 0; v < w; ++v) run += part[v];
   for (int64_t k = b; k < e; ++k) {
-    const int64_t c = ws[k];
-    ws[k] = run;
+    const int64_t c = ws[k * stride];
+    ws[k * stride] = run;
     run += c;
   }
-  if (t == 1023) *count = part[1023];
+  if (t == 1023) *count = run;
 }
 
+template <int R>
 __global__ void __launch_bounds__(256) unw_write_kernel(const double* __restrict__ f, int64_t n,
                                                         double fmax, uint64_t seed, int64_t off,
+                                                        int64_t slots,
                                                         const int64_t* __restrict__ ws,
                                                         int64_t* __restrict__ idx) {
-  __shared__ int cnt[4];
+  constexpr int C = 4 * R;
+  __shared__ uint64_t kept[C];
+  __shared__ int before[C];
   const int t = threadIdx.x, w = t >> 6, l = t & 63;
-  const int64_t i = (int64_t)blockIdx.x * 256 + t;
-  const bool k = keep(f, i, n, fmax, seed, off);
-  const uint64_t m = __ballot(k);
-  if (l == 0) cnt[w] = __popcll(m);
+  const int64_t k = (int64_t)blockIdx.x * R;
+  const int64_t i0 = (int64_t)blockIdx.x * (256 * R) + t;
+  const uint64_t any = R > 1 && k + 1 < slots ? (uint64_t)ws[k + 1] : ~0ull;
+  if (any == 0) return;
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const int c = 4 * q + w;
+    uint64_t m = 0;
+    if ((any >> c) & 1) {
+      const int64_t i = i0 + 256 * q;
+      m = __ballot(keep(weight_at(f, i, n), i, fmax, seed, off));
+    }
+    if (l == 0) kept[c] = m;
+  }
   __syncthreads();
-  int64_t base = ws[blockIdx.x];
-  for (int v = 0; v < w; ++v) base += cnt[v];
-  if (k) idx[base + __popcll(m & ((1ull << l) - 1ull))] = i;
+  if (w == 0) {
+    const int64_t p = l < C ? __popcll(kept[l]) : 0;
+    const int64_t incl = wave_prefix(p, l);
+    if (l < C) before[l] = (int)(incl - p);
+  }
+  __syncthreads();
+  const int64_t base = ws[k];
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const int c = 4 * q + w;
+    const uint64_t m = kept[c];
+    if ((m >> l) & 1) idx[base + before[c] + __popcll(m & ((1ull << l) - 1ull))] = i0 + 256 * q;
+  }
 }
 
 // Fixed device scratch of the allocation-free unweighting entry point: one
@@ -204,13 +256,30 @@ int launch_xsec_stats(const double* f, int64_t n, double* out, double* ws, hipSt
 
 int64_t unweight_blocks(int64_t n) { return (n + 255) / 256; }
 
+template <int R>
+static void unweight_kernels(const double* f, int64_t n, double fmax, uint64_t seed, int64_t off,
+                             int64_t* idx, int64_t* count, int64_t* ws, int64_t slots,
+                             hipStream_t s) {
+  const int64_t nb = (slots + R - 1) / R;
+  if (nb > 0)
+    unw_count_kernel<R><<<(unsigned)nb, 256, 0, s>>>(f, n, fmax, seed, off, slots, ws);
+  unw_scan_kernel<<<1, 1024, 0, s>>>(ws, nb, R, count);  // nb = 0: writes count = 0
+  if (nb > 0)
+    unw_write_kernel<R><<<(unsigned)nb, 256, 0, s>>>(f, n, fmax, seed, off, slots, ws, idx);
+}
+
+// Groups of 256 events per block: as many as leave about a thousand blocks (four
+// per CU), so that the one block of the scan has few counts to go through (5e6
+// events: 19532 counts in 34.6 us with one group per block, 1221 in 5.0 us
+// with 16) and the second pass draws random numbers for the chunks with kept
+// events only.
 int launch_unweight(const double* f, int64_t n, double fmax, uint64_t seed, int64_t off,
                     int64_t* idx, int64_t* count, int64_t* ws, hipStream_t s) {
-  const int64_t nb = unweight_blocks(n);
-  if (nb > 0x7FFFFFFF) return -1;
-  if (nb > 0) unw_count_kernel<<<(unsigned)nb, 256, 0, s>>>(f, n, fmax, seed, off, ws);
-  unw_scan_kernel<<<1, 1024, 0, s>>>(ws, nb, count);  // nb = 0: writes count = 0
-  if (nb > 0) unw_write_kernel<<<(unsigned)nb, 256, 0, s>>>(f, n, fmax, seed, off, ws, idx);
+  const int64_t slots = unweight_blocks(n);
+  if (slots > 0x7FFFFFFF) return -1;
+  if (n > (1 << 22)) unweight_kernels<16>(f, n, fmax, seed, off, idx, count, ws, slots, s);
+  else if (n > (1 << 20)) unweight_kernels<4>(f, n, fmax, seed, off, idx, count, ws, slots, s);
+  else unweight_kernels<1>(f, n, fmax, seed, off, idx, count, ws, slots, s);
   return 0;
 }
 
