@@ -100,11 +100,13 @@ def _ptr(t):
         raise ValueError("expected a device tensor")
     if not t.is_contiguous():
         raise ValueError("expected a contiguous tensor")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream(device):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    # torch.cuda.current_stream(device).cuda_stream without the Stream object
+    # that it makes for every call (0.1 against 1.6 us of a 6 us call)
+    return torch._C._cuda_getCurrentRawStream(device.index)
 
 
 class MEEngine:
@@ -173,10 +175,16 @@ class MEEngine:
     def events_rnd(self, r):
         lay = self.layout
         nevt = r.shape[0]
-        npg = self._pages(nevt, lay.neppR)
-        buf = torch.full((npg * lay.neppR, lay.nrnd), 0.5, dtype=torch.float64, device=self.device)
-        buf[:nevt] = r.to(self.device, torch.float64)
-        return buf.view(npg, lay.neppR, lay.nrnd).permute(0, 2, 1).contiguous().view(-1)
+        r = r.to(self.device, torch.float64)
+        buf = torch.empty(self._pages(nevt, lay.neppR), lay.nrnd, lay.neppR, dtype=torch.float64,
+                          device=self.device)
+        full, rest = divmod(nevt, lay.neppR)
+        if full:  # whole pages in one transposing copy
+            buf[:full] = r[:nevt - rest].unflatten(0, (full, lay.neppR)).transpose(1, 2)
+        if rest:
+            buf[full] = 0.5
+            buf[full, :, :rest] = r[nevt - rest:].t()
+        return buf.view(-1)
 
     # ------------------------------------------------------------ the path
     def rng(self, seed, nevt, offset=0, out=None):
