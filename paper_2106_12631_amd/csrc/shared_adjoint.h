@@ -16,12 +16,13 @@
 // event per lane with a helicity loop and 8 dual RAMBO passes: 671 and 167 us).
 // g g -> t t~ g: 16 lanes an event, one per helicity of the gluons and the t~,
 // since the accumulators of both t~ helicities do not fit the registers (8
-// lanes: 1.6 KB of scratch a lane, 3.2 ms).  2^18 events in 1.57 ms, 70 events
-// in 37 us (3.99 and 1.05 ms with one event per lane).  Bound: FP64 VALU
-// latency at one wave per SIMD of 512 registers; the U(a) and the adjoints of
-// the flows wait in LDS (36 KB a wave), and identical forward values are
-// computed again in the reverse sweep rather than kept (pin below: without it
-// 2.3 KB of scratch and 6.8 ms).
+// lanes: 1.6 KB of scratch a lane, 3.2 ms).  2^18 events in 1.21 ms, 70 events
+// in 33 us (3.97 and 1.05 ms with one event per lane).  Bound: FP64 VALU
+// latency at one wave per SIMD of 512 registers; the U(a), the adjoints of
+// the flows and the momenta wait in LDS (36 KB a wave; momenta in registers
+// cost 75 reloads from scratch, one after the other: 1.56 ms), and identical
+// forward values are computed again in the reverse sweep rather than kept (pin
+// below: without it 2.3 KB of scratch and 6.8 ms).
 //
 // Adjoints follow helas_adj.h: zb = dL/d(Re z) + i dL/d(Im z).
 #pragma once
@@ -328,7 +329,7 @@ struct GradGGTT : GGTT<true, ColourSum<P>> {
 
 template <class P>
 struct GradGGTTG : GGTTG<true, ColourSum<P>> {
-  static constexpr int LANES = 16, LDS = 9 * 256;
+  static constexpr int LANES = 16, EVENT = 9 * 256, LDS = EVENT + 4 * 6;
   using B = GGTTG<true, ColourSum<P>>;
   using B::u; using B::v; using B::k; using B::cp;
   __device__ __forceinline__ GradGGTTG(const double (&p)[5][4], const Couplings<double>& c)
@@ -344,8 +345,21 @@ struct GradGGTTG : GGTTG<true, ColourSum<P>> {
     pin(eb[1], eb[2], eb[3].r);
   }
 
+  // momentum of leg 2 + l, read again at each use
+  __device__ __forceinline__ static void momentum(const d2* lds, int& at, int l, double (&q)[4]) {
+    asm volatile("" : "+v"(at));
+    lds_get_real(lds + at + 2 * l, q);
+  }
+
   __device__ __forceinline__ double gradient(const double (&p)[5][4], int g, uint64_t mask,
-                                             d2* park, double (&pb)[P::NPAR][4]) {
+                                             d2* lds, double (&pb)[P::NPAR][4]) {
+    d2* park = lds + threadIdx.x;
+    int at = EVENT + 6 * (threadIdx.x / LANES);
+#pragma unroll
+    for (int l = 0; l < 3; ++l) {  // the same from each lane of the event
+      lds[at + 2 * l] = d2{p[l + 2][0], p[l + 2][1]};
+      lds[at + 2 * l + 1] = d2{p[l + 2][2], p[l + 2][3]};
+    }
     c64 e[3][4], J[3][4], M[2][4];
     const int tb = g & 1, lam2 = g & 2 ? 1 : -1;
     B::gluon_currents(g & 8 ? 1 : -1, g & 4 ? 1 : -1, lam2, e, J, M);
@@ -361,9 +375,10 @@ struct GradGGTTG : GGTTG<true, ColourSum<P>> {
       for (int a = 0; a < 3; ++a) {
         pin(u[t]);
         c64 s[4], o[4];
-        double q[4];
+        double q[4], pt[4];
+        momentum(lds, at, 0, pt);
         slash_col(e[a], u[t], s);
-        minus4(p[2], k[a], q);
+        minus4(pt, k[a], q);
         propagate(q, cp.mt, factor(q, a), s, o);
         pin(o);
         lds_put(park + (t * 3 + a) * 256, 64, o);
@@ -391,9 +406,10 @@ struct GradGGTTG : GGTTG<true, ColourSum<P>> {
       for (int a = 0; a < 3; ++a) {
         pin(vt);
         c64 s[4];
-        double q[4];
+        double q[4], pa[4];
+        momentum(lds, at, 1, pa);
         slash_col(e[a], vt, s);
-        minus4(k[a], p[3], q);
+        minus4(k[a], pa, q);
         propagate(q, cp.mt, factor(q, a), s, W[a]);
         pin(W[a]);
       }
@@ -586,10 +602,11 @@ struct GradGGTTG : GGTTG<true, ColourSum<P>> {
         for (int t = 0; t < 2; ++t) {
           // U = d (q-slash + m) e-slash u, q = p(t) - k
           c64 s[4], fb[4];
-          double q[4], kb[4] = {0.0, 0.0, 0.0, 0.0};
+          double q[4], pt[4], kb[4] = {0.0, 0.0, 0.0, 0.0};
+          momentum(lds, at, 0, pt);
           pin(u[t]);
           slash_col(e[a], u[t], s);
-          minus4(p[2], k[a], q);
+          minus4(pt, k[a], q);
           adj_propagate(q, cp.mt, ig, factor(q, a), s, Ub[t], fb, kb);
           adj_slash_spinor(e[a], fb, ub[t]);
           if (a == 2) adj_slash_vector(u[t], fb, eb);
@@ -610,9 +627,10 @@ struct GradGGTTG : GGTTG<true, ColourSum<P>> {
         pin(vt, Wb[a]);
         if (a == 2) pin_eps(e[2]);
         c64 s[4], fb[4];
-        double q[4], kb[4] = {0.0, 0.0, 0.0, 0.0};
+        double q[4], pa[4], kb[4] = {0.0, 0.0, 0.0, 0.0};
+        momentum(lds, at, 1, pa);
         slash_col(e[a], vt, s);
-        minus4(k[a], p[3], q);
+        minus4(k[a], pa, q);
         adj_propagate(q, cp.mt, ig, factor(q, a), s, Wb[a], fb, kb);
         adj_slash_spinor(e[a], fb, vb);
         if (a == 2) adj_slash_vector(vt, fb, eb);
@@ -628,20 +646,16 @@ struct GradGGTTG : GGTTG<true, ColourSum<P>> {
         }
       }
     double pt[4], pa[4], pg[4];
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      pt[m] = p[2][m];
-      pa[m] = p[3][m];
-      pg[m] = p[4][m];
-    }
+    momentum(lds, at, 1, pa);
     pin(pa, vb);
     qb.add(pa, cp.mt, true, tb, vb);
     qb.finish(pa, cp.mt, pb[3]);
+    momentum(lds, at, 0, pt);
     pin(pt, ub[0], ub[1], pb[3]);
 #pragma unroll
     for (int t = 0; t < 2; ++t) qt.add(pt, cp.mt, false, t, ub[t]);
     qt.finish(pt, cp.mt, pb[2]);
-    pin(pb[2], pg);
+    pin(pb[2]);
 #pragma unroll
     for (int c = 0; c < 2; ++c) {  // J[c] = -f[c] L(e[a], e[2]), a = 1 - c
       const int a = 1 - c;
@@ -657,6 +671,7 @@ struct GradGGTTG : GGTTG<true, ColourSum<P>> {
     }
 #pragma unroll
     for (int m = 0; m < 4; ++m) pb[4][m] -= k2b[m];
+    momentum(lds, at, 2, pg);
     adj_polarisation(pg, lam2, eb, pb[4]);
     }
     return me;
@@ -689,10 +704,14 @@ __global__ void __launch_bounds__(64)
   for (int l = 0; l < NP; ++l)
 #pragma unroll
     for (int m = 0; m < 4; ++m) pb[l][m] = 0.0;
-  const double me = lanes_sum<L>(Event(p, c).gradient(p, g, mask, lds + threadIdx.x, pb));
+  const double me = lanes_sum<L>(Event(p, c).gradient(p, g, mask, lds, pb));
 #pragma unroll
   for (int l = 0; l < NF; ++l) {
     // dE = p.dp / E on the mass shell
+    if constexpr (L == 16) {
+      int at = Event::EVENT + 6 * (threadIdx.x / L);
+      Event::momentum(lds, at, l, p[l + 2]);
+    }
     const double e = lanes_sum<L>(pb[l + 2][0]) * recip(p[l + 2][0]);
 #pragma unroll
     for (int m = 1; m < 4; ++m) {
