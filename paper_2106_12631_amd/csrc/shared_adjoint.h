@@ -16,13 +16,16 @@
 // event per lane with a helicity loop and 8 dual RAMBO passes: 671 and 167 us).
 // g g -> t t~ g: 16 lanes an event, one per helicity of the gluons and the t~,
 // since the accumulators of both t~ helicities do not fit the registers (8
-// lanes: 1.6 KB of scratch a lane, 3.2 ms).  2^18 events in 1.21 ms, 70 events
-// in 33 us (3.97 and 1.05 ms with one event per lane).  Bound: FP64 VALU
-// latency at one wave per SIMD of 512 registers; the U(a), the adjoints of
-// the flows and the momenta wait in LDS (36 KB a wave; momenta in registers
-// cost 75 reloads from scratch, one after the other: 1.56 ms), and identical
-// forward values are computed again in the reverse sweep rather than kept (pin
-// below: without it 2.3 KB of scratch and 6.8 ms).
+// lanes: 1.6 KB of scratch a lane, 3.2 ms).  The U(a) and W(a) depend on one
+// gluon's helicity: a lane forms one of each, and their adjoints, summed over
+// the lanes of a version through LDS, are taken on by one lane (each lane for
+// itself: 1.21 ms).  2^18 events in 0.99 ms, 70 events in 29 us (3.97 and
+// 1.05 ms with one event per lane).  Bound: FP64 VALU at one wave per SIMD of
+// 512 registers, 6.4e3 instructions a wave, 14 % of them copies to and from
+// AGPRs; versions, adjoints of the flows and momenta wait in LDS (35 KB a wave;
+// momenta in registers cost 75 reloads from scratch, one after the other), and
+// identical forward values are computed again in the reverse sweep rather than
+// kept (pin below: without it 2.3 KB of scratch and 6.8 ms).
 //
 // Adjoints follow helas_adj.h: zb = dL/d(Re z) + i dL/d(Im z).
 #pragma once
@@ -329,17 +332,18 @@ struct GradGGTT : GGTT<true, ColourSum<P>> {
 
 template <class P>
 struct GradGGTTG : GGTTG<true, ColourSum<P>> {
-  static constexpr int LANES = 16, EVENT = 9 * 256, LDS = EVENT + 4 * 6;
+  // LDS in complex numbers: the versions of U and of W, component-major (an
+  // event has 12 of each: quark helicity, gluon, gluon helicity), the adjoints
+  // of the flows, U's adjoints of the 64 lanes on their way to the sum over the
+  // lanes of a version (those of gluon 2 in the place of flows already used),
+  // the momenta
+  static constexpr int LANES = 16, SU = 0, SW = SU + 192, FLOW = SW + 192, UB = FLOW + 12 * 64,
+                       EVENT = UB + 4 * 256, LDS = EVENT + 4 * 6;
   using B = GGTTG<true, ColourSum<P>>;
   using B::u; using B::v; using B::k; using B::cp;
   __device__ __forceinline__ GradGGTTG(const double (&p)[5][4], const Couplings<double>& c)
       : B(p, c) {}
 
-  // propagator factors along the quark line; formed where they are used, they
-  // take no registers in between
-  __device__ __forceinline__ c64 factor(const double (&q)[4], int a) const {
-    return quark_factor(q, cp.mt, a < 2 ? cp.wtt : cp.wt, cp.gs);
-  }
   // what the reverse sweep needs of the polarisation's adjoint
   __device__ __forceinline__ static void pin_eps(c64 (&eb)[4]) {
     pin(eb[1], eb[2], eb[3].r);
@@ -353,8 +357,8 @@ struct GradGGTTG : GGTTG<true, ColourSum<P>> {
 
   __device__ __forceinline__ double gradient(const double (&p)[5][4], int g, uint64_t mask,
                                              d2* lds, double (&pb)[P::NPAR][4]) {
-    d2* park = lds + threadIdx.x;
-    int at = EVENT + 6 * (threadIdx.x / LANES);
+    const int lane = threadIdx.x;
+    int at = EVENT + 6 * (lane / LANES);
 #pragma unroll
     for (int l = 0; l < 3; ++l) {  // the same from each lane of the event
       lds[at + 2 * l] = d2{p[l + 2][0], p[l + 2][1]};
@@ -363,26 +367,56 @@ struct GradGGTTG : GGTTG<true, ColourSum<P>> {
     c64 e[3][4], J[3][4], M[2][4];
     const int tb = g & 1, lam2 = g & 2 ? 1 : -1;
     B::gluon_currents(g & 8 ? 1 : -1, g & 4 ? 1 : -1, lam2, e, J, M);
-    c64 vt[4];
+    // U and W depend on one gluon's helicity: each is formed by one lane of the
+    // event, that of gluon `own` at the lane's helicity of it and of the quark
+    // (two lanes in eight are spare: they repeat gluon 0)
+    const int l0 = (g >> 3) & 1, l1 = (g >> 2) & 1, l2 = (g >> 1) & 1;
+    const int own = l0 == l1 ? (l1 == l2 ? 0 : 1) : (l0 == l2 ? 2 : 0);
+    const bool spare = l0 != l1 && l1 == l2;
+    const int ver = 12 * (lane / LANES);
+    auto version = [&](int q, int a, int l) { return ver + 2 * (3 * q + a) + l; };
+    const int mine = version(tb, own, own == 0 ? l0 : own == 1 ? l1 : l2);
+    auto pick = [&](double x0, double x1, double x2) { return own == 0 ? x0 : own == 1 ? x1 : x2; };
+    c64 vt[4], ut[4], ea[4];
+    double ka[4];
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
       vt[m].r = tb ? v[1][m].r : v[0][m].r;
       vt[m].i = tb ? v[1][m].i : v[0][m].i;
+      ut[m].r = tb ? u[1][m].r : u[0][m].r;
+      ut[m].i = tb ? u[1][m].i : u[0][m].i;
     }
+    auto own_gluon = [&]() {
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        pin(u[t]);
-        c64 s[4], o[4];
-        double q[4], pt[4];
-        momentum(lds, at, 0, pt);
-        slash_col(e[a], u[t], s);
-        minus4(pt, k[a], q);
-        propagate(q, cp.mt, factor(q, a), s, o);
-        pin(o);
-        lds_put(park + (t * 3 + a) * 256, 64, o);
+      for (int m = 0; m < 4; ++m) {
+        ea[m].r = pick(e[0][m].r, e[1][m].r, e[2][m].r);
+        ea[m].i = pick(e[0][m].i, e[1][m].i, e[2][m].i);
+        ka[m] = pick(k[0][m], k[1][m], k[2][m]);
       }
+    };
+    auto own_factor = [&](const double (&q)[4]) {
+      return quark_factor(q, cp.mt, own < 2 ? cp.wtt : cp.wt, cp.gs);
+    };
+    own_gluon();
+    {
+      c64 s[4], o[4];
+      double q[4], pq[4];
+      momentum(lds, at, 0, pq);
+      slash_col(ea, ut, s);
+      minus4(pq, ka, q);
+      propagate(q, cp.mt, own_factor(q), s, o);
+      lds_put(lds + SU + mine, 48, o);
+      momentum(lds, at, 1, pq);
+      slash_col(ea, vt, s);
+      minus4(ka, pq, q);
+      propagate(q, cp.mt, own_factor(q), s, o);
+      lds_put(lds + SW + mine, 48, o);
+      pin(ut, ea, ka);
+    }
+    __syncthreads();
+    auto get_U = [&](int t, int a, c64 (&w)[4]) {
+      lds_get(lds + SU + version(t, a, a == 0 ? l0 : a == 1 ? l1 : l2), 48, w);
+    };
     // adjoints: u, e[2], J[0], J[1] (J[2] and e[0], e[1] have no derivative), M, k[2]
     c64 ub[2][4], eb[4], Jb[2][4], Mb[2][4];
     double k2b[4] = {0.0, 0.0, 0.0, 0.0};
@@ -399,18 +433,13 @@ struct GradGGTTG : GGTTG<true, ColourSum<P>> {
     const int code = ((g & 12) << 1) | (tb << 1) | ((g >> 1) & 1);
     const c64 z{0.0, 0.0};
     c64 W[3][4];
-    d2* flow = park + 6 * 256;  // adjoints of the flows: flow t * 6 + k at [64 (t * 6 + k)]
-    auto flow_adjoint = [&](int t, int k) { return lds_scalar(flow + 64 * (6 * t + k)); };
+    // adjoints of the flows: flow k of t helicity t at [64 (2 k + t)]
+    d2* flow = lds + FLOW + lane;
+    auto flow_adjoint = [&](int t, int k) { return lds_scalar(flow + 64 * (2 * k + t)); };
     {
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
-        pin(vt);
-        c64 s[4];
-        double q[4], pa[4];
-        momentum(lds, at, 1, pa);
-        slash_col(e[a], vt, s);
-        minus4(k[a], pa, q);
-        propagate(q, cp.mt, factor(q, a), s, W[a]);
+        lds_get(lds + SW + version(tb, a, a == 0 ? l0 : a == 1 ? l1 : l2), 48, W[a]);
         pin(W[a]);
       }
       {
@@ -421,7 +450,7 @@ struct GradGGTTG : GGTTG<true, ColourSum<P>> {
           pin(vt, W[b], W[c]);
           c64 U[2][4];
 #pragma unroll
-          for (int t = 0; t < 2; ++t) lds_get(park + (t * 3 + a) * 256, 64, U[t]);
+          for (int t = 0; t < 2; ++t) get_U(t, a, U[t]);
           slash_col(J[a], vt, s);
 #pragma unroll
           for (int m = 0; m < 4; ++m) r[m] = s[m];
@@ -470,7 +499,7 @@ struct GradGGTTG : GGTTG<true, ColourSum<P>> {
           me += adj_colour<P>(A[t], (mask >> h) & 1 ? cp.gs2 : 0.0, Ab);
           pin(Ab[0], Ab[1], Ab[2], Ab[3], Ab[4], Ab[5], me);
 #pragma unroll
-          for (int k = 0; k < 6; ++k) flow[64 * (6 * t + k)] = d2{Ab[k].r, Ab[k].i};
+          for (int k = 0; k < 6; ++k) flow[64 * (2 * k + t)] = d2{Ab[k].r, Ab[k].i};
         }
       }
       // ---- reverse -------------------------------------------------------
@@ -544,15 +573,17 @@ struct GradGGTTG : GGTTG<true, ColourSum<P>> {
       clear4(Wb[2]);
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
+        const int a = c == 0 ? 1 : 0, b = c == 2 ? 1 : 2;
+        const c64 xb[2] = {flow_adjoint(0, 2 * a + (b > c)) - flow_adjoint(0, 2 * b + (a > c)),
+                           flow_adjoint(1, 2 * a + (b > c)) - flow_adjoint(1, 2 * b + (a > c))};
         pin(W[c], u[0], u[1]);
         if (c < 2) pin(J[c]);
-        const int a = c == 0 ? 1 : 0, b = c == 2 ? 1 : 2;
         c64 s[4], sb[4];
         slash_col(J[c], W[c], s);
         clear4(sb);
 #pragma unroll
         for (int t = 0; t < 2; ++t)
-          adj_sdot(u[t], s, flow_adjoint(t, 2 * a + (b > c)) - flow_adjoint(t, 2 * b + (a > c)), ub[t], sb);
+          adj_sdot(u[t], s, xb[t], ub[t], sb);
         adj_slash_spinor(J[c], sb, Wb[c]);
         if (c < 2) adj_slash_vector(W[c], sb, Jb[c]);
         pin(ub[0], ub[1], Wb[c]);
@@ -570,8 +601,12 @@ struct GradGGTTG : GGTTG<true, ColourSum<P>> {
 #pragma unroll
         for (int o = 0; o < 2; ++o) {  // U(a).r, r = +-J-slash(a) v + e-slash(x) W(y)
           const int x = o ? c : b, y = o ? b : c;
+          // read before they are needed: a read stops at the next pin
+          c64 U[2][4], r[4], rb[4];
+          const c64 Ab[2] = {flow_adjoint(0, 2 * a + o), flow_adjoint(1, 2 * a + o)};
+          get_U(0, a, U[0]);
+          get_U(1, a, U[1]);
           pin(vt, W[y]);
-          c64 r[4], rb[4];
           slash_col(J[a], vt, r);
           if (o) {
 #pragma unroll
@@ -582,9 +617,7 @@ struct GradGGTTG : GGTTG<true, ColourSum<P>> {
           pin(r);
 #pragma unroll
           for (int t = 0; t < 2; ++t) {
-            c64 U[4];
-            lds_get(park + (t * 3 + a) * 256, 64, U);
-            adj_sdot(U, r, flow_adjoint(t, 2 * a + o), Ub[t], rb);
+            adj_sdot(U[t], r, Ab[t], Ub[t], rb);
             pin(Ub[t], rb);
           }
           adj_slash_spinor(e[x], rb, Wb[y]);
@@ -598,52 +631,85 @@ struct GradGGTTG : GGTTG<true, ColourSum<P>> {
         if (a < 2) adj_slash_vector(vt, sb, Jb[a]);
         pin(vb);
         if (a < 2) pin(Jb[a]);
+        // on to the lanes that sum them
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          // U = d (q-slash + m) e-slash u, q = p(t) - k
-          c64 s[4], fb[4];
-          double q[4], pt[4], kb[4] = {0.0, 0.0, 0.0, 0.0};
-          momentum(lds, at, 0, pt);
-          pin(u[t]);
-          slash_col(e[a], u[t], s);
-          minus4(pt, k[a], q);
-          adj_propagate(q, cp.mt, ig, factor(q, a), s, Ub[t], fb, kb);
-          adj_slash_spinor(e[a], fb, ub[t]);
-          if (a == 2) adj_slash_vector(u[t], fb, eb);
-#pragma unroll
-          for (int m = 0; m < 4; ++m) {
-            pb[2][m] += kb[m];
-            if (a == 2) k2b[m] -= kb[m];
-          }
-          pin(ub[t], pb[2]);
-          if (a == 2) {
-            pin(k2b);
-            pin_eps(eb);
-          }
-        }
+        for (int t = 0; t < 2; ++t)
+          lds_put(lds + (a < 2 ? UB + 512 * a : FLOW) + 256 * t + lane, 64, Ub[t]);
       }
+      __syncthreads();
+      // U = d (q-slash + m) e-slash u, q = p(t) - k, of the lane's own version:
+      // its adjoint is the sum over the lanes with the same gluon helicity
+      const int b1 = own == 2 ? 4 : 2, b2 = own == 0 ? 4 : 8;
+      const double last = own == 2 ? 1.0 : 0.0;  // gluon 2: its momentum and polarisation move
+      auto own_adjoint = [&](const c64 (&f)[4], const double (&q)[4], const c64 (&ob)[4],
+                             c64 (&fb)[4], double (&kb)[4]) {
+        c64 s[4];
+        slash_col(ea, f, s);
+        adj_propagate(q, cp.mt, ig, own_factor(q), s, ob, fb, kb);
+        c64 x[4];
 #pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        pin(vt, Wb[a]);
-        if (a == 2) pin_eps(e[2]);
-        c64 s[4], fb[4];
-        double q[4], pa[4], kb[4] = {0.0, 0.0, 0.0, 0.0};
-        momentum(lds, at, 1, pa);
-        slash_col(e[a], vt, s);
-        minus4(k[a], pa, q);
-        adj_propagate(q, cp.mt, ig, factor(q, a), s, Wb[a], fb, kb);
-        adj_slash_spinor(e[a], fb, vb);
-        if (a == 2) adj_slash_vector(vt, fb, eb);
+        for (int m = 0; m < 4; ++m) x[m] = last * fb[m];
+        adj_slash_vector(f, x, eb);
+      };
+      {
+        c64 sum[4], fb[4], fu[4];
+        double q[4], pq[4], kb[4] = {0.0, 0.0, 0.0, 0.0};
+        clear4(sum);
+        const d2* from = lds + (own == 0 ? UB : own == 1 ? UB + 512 : FLOW) + 256 * tb;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          c64 x[4];
+          lds_get(from + (lane ^ ((j & 1) | (j & 2 ? b1 : 0) | (j & 4 ? b2 : 0))), 64, x);
+#pragma unroll
+          for (int m = 0; m < 4; ++m) sum[m] = sum[m] + x[m];
+        }
+#pragma unroll
+        for (int m = 0; m < 4; ++m) sum[m] = spare ? c64{0.0, 0.0} : sum[m];
+        momentum(lds, at, 0, pq);
+        pin(sum, ut, ea, ka);
+        minus4(pq, ka, q);
+        own_adjoint(ut, q, sum, fb, kb);
+        clear4(fu);
+        adj_slash_spinor(ea, fb, fu);
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+          ub[0][m] = rmadd(tb ? 0.0 : 1.0, fu[m], ub[0][m]);
+          ub[1][m] = rmadd(tb ? 1.0 : 0.0, fu[m], ub[1][m]);
+          pb[2][m] += kb[m];
+          k2b[m] = fmadd(-last, kb[m], k2b[m]);
+        }
+        pin(ub[0], ub[1], pb[2], k2b);
+        pin_eps(eb);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int a = 0; a < 3; ++a) lds_put(lds + UB + 256 * a + lane, 64, Wb[a]);
+      __syncthreads();
+      {
+        c64 sum[4], fb[4];
+        double q[4], pq[4], kb[4] = {0.0, 0.0, 0.0, 0.0};
+        clear4(sum);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          c64 x[4];
+          lds_get(lds + UB + 256 * own + (lane ^ ((j & 1 ? b1 : 0) | (j & 2 ? b2 : 0))), 64, x);
+#pragma unroll
+          for (int m = 0; m < 4; ++m) sum[m] = sum[m] + x[m];
+        }
+#pragma unroll
+        for (int m = 0; m < 4; ++m) sum[m] = spare ? c64{0.0, 0.0} : sum[m];
+        momentum(lds, at, 1, pq);
+        pin(sum, vt, ea, ka);
+        minus4(ka, pq, q);
+        own_adjoint(vt, q, sum, fb, kb);
+        adj_slash_spinor(ea, fb, vb);
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
           pb[3][m] -= kb[m];
-          if (a == 2) k2b[m] += kb[m];
+          k2b[m] = fmadd(last, kb[m], k2b[m]);
         }
-        pin(vb, pb[3]);
-        if (a == 2) {
-          pin(k2b);
-          pin_eps(eb);
-        }
+        pin(vb, pb[3], k2b);
+        pin_eps(eb);
       }
     double pt[4], pa[4], pg[4];
     momentum(lds, at, 1, pa);
