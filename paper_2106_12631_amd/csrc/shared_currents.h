@@ -901,7 +901,7 @@ struct GGTT {
 
 template <bool BEAM, class Sum>
 struct GGTTG {
-  c64 u[2][4], v[2][4], dU[3], dW[3];
+  c64 u[2][4], v[2][4];
   double k[3][4], pt[4], pb[4], f[3], f012;  // f[c]: g / K^2 of the pair without c
   Couplings<double> cp;
 
@@ -925,14 +925,6 @@ struct GGTTG {
     f[1] = c.gs * recip(msq(K));
     plus4(k[1], k[2], K);
     f[0] = c.gs * recip(msq(K));
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const double w = a < 2 ? c.wtt : c.wt;
-      minus4(p[2], k[a], K);
-      dU[a] = quark_factor(K, c.mt, w, c.gs);
-      minus4(k[a], p[3], K);
-      dW[a] = quark_factor(K, c.mt, w, c.gs);
-    }
   }
 
   // polarisation vectors, J[c]: the pair without c, M[m]: J(x m y), m in the middle
@@ -974,40 +966,69 @@ struct GGTTG {
     }
   }
 
-  // park: this lane's slots for U(a), component k of slot s at [256 s + 64 k].
+  // Gluon whose U and W the lane of gluon helicities (l0 l1 l2) forms, at its
+  // own helicity of it: the versions of the three gluons are all covered
+  // (two lanes in eight repeat a version of gluon 0)
+  __device__ __forceinline__ static int own_gluon(int l0, int l1, int l2) {
+    return l0 == l1 ? (l1 == l2 ? 0 : 1) : (l0 == l2 ? 2 : 0);
+  }
+
+  // lds: the wave's slots; ev: the event's number in the wave, lane: the lane's.
   // A(abc) / g = U(a).(b-slash W(c) + J-slash(bc) v) + u.(J-slash(ab) W(c) + J-slash(abc) v)
+  static constexpr int SU = 0, SW = SU + 4 * 96, SM = SW + 4 * 96, LDS = SM + 8 * 64;
   template <class Emit>
-  __device__ __forceinline__ void flows_sum(int lam0, int lam1, int lam2, d2* park, Emit emit) {
-    c64 e[3][4], J[3][4], M[2][4];
-    gluon_currents(lam0, lam1, lam2, e, J, M);
+  __device__ __forceinline__ void flows_sum(int l0, int l1, int l2, d2* lds, int ev, int lane,
+                                            Emit emit) {
+    c64 e[3][4], J[3][4];
+    const int ver = 12 * ev;
+    auto version = [&](int q, int a) { return ver + 6 * q + 2 * a + (a == 0 ? l0 : a == 1 ? l1 : l2); };
+    {
+      c64 M[2][4];
+      gluon_currents(2 * l0 - 1, 2 * l1 - 1, 2 * l2 - 1, e, J, M);
+      lds_put(lds + SM + lane, 64, M[0]);
+      lds_put(lds + SM + 256 + lane, 64, M[1]);
+      const int own = own_gluon(l0, l1, l2);
+      auto pick = [&](double x0, double x1, double x2) { return own == 0 ? x0 : own == 1 ? x1 : x2; };
+      const int mine = ver + 2 * own + (own == 0 ? l0 : own == 1 ? l1 : l2);
+      const double w = own < 2 ? cp.wtt : cp.wt;
+      c64 ea[4], s[4], o[4];
+      double ka[4], q[4];
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        c64 s[4], o[4];
-        double q[4];
-        slash_col(e[a], u[t], s);
-        minus4(pt, k[a], q);
-        propagate(q, cp.mt, dU[a], s, o);
-        lds_put(park + (t * 3 + a) * 256, 64, o);
+      for (int m = 0; m < 4; ++m) {
+        ea[m].r = pick(e[0][m].r, e[1][m].r, e[2][m].r);
+        ea[m].i = pick(e[0][m].i, e[1][m].i, e[2][m].i);
+        ka[m] = pick(k[0][m], k[1][m], k[2][m]);
       }
+      minus4(pt, ka, q);
+      c64 d = quark_factor(q, cp.mt, w, cp.gs);
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        slash_col(ea, u[t], s);
+        propagate(q, cp.mt, d, s, o);
+        lds_put(lds + SU + mine + 6 * t, 96, o);
+      }
+      minus4(ka, pb, q);
+      d = quark_factor(q, cp.mt, w, cp.gs);
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        slash_col(ea, v[t], s);
+        propagate(q, cp.mt, d, s, o);
+        lds_put(lds + SW + mine + 6 * t, 96, o);
+      }
+    }
+    __syncthreads();
     auto of_antiquark = [&](int tb) {
       __builtin_amdgcn_sched_barrier(0);
       c64 W[3][4], A[2][6], s[4], r[4];
 #pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        slash_col(e[a], v[tb], s);
-        double q[4];
-        minus4(k[a], pb, q);
-        propagate(q, cp.mt, dW[a], s, W[a]);
-      }
+      for (int a = 0; a < 3; ++a) lds_get(lds + SW + version(tb, a), 96, W[a]);
       // ordering (a b c): rank 2 a + (b > c)
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
         const int b = a == 0 ? 1 : 0, c = a == 2 ? 1 : 2;
         c64 U[2][4];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) lds_get(park + (t * 3 + a) * 256, 64, U[t]);
+        for (int t = 0; t < 2; ++t) lds_get(lds + SU + version(t, a), 96, U[t]);
         slash_col(J[a], v[tb], s);
 #pragma unroll
         for (int m = 0; m < 4; ++m) r[m] = s[m];
@@ -1034,7 +1055,9 @@ struct GGTTG {
       c64 y[2][2];
 #pragma unroll
       for (int m = 0; m < 2; ++m) {
-        slash_col(M[m], v[tb], s);
+        c64 M[4];
+        lds_get(lds + SM + 256 * m + lane, 64, M);
+        slash_col(M, v[tb], s);
 #pragma unroll
         for (int t = 0; t < 2; ++t) y[t][m] = sdot_add(u[t], s, c64{0.0, 0.0});
       }
@@ -1164,8 +1187,12 @@ __device__ __forceinline__ void ggtt_shared(const double (&p)[4][4], const Coupl
 
 // Eight lanes per event, one for each helicity of the three gluons, each with
 // the four quark helicities; the sum over the lanes is a DPP butterfly.  The
-// t-side spinors U(a) wait in LDS (24 KB a wave): in registers they cost
-// 608 bytes of scratch a lane and 11 % more time.
+// U(a) and W(a) depend on one gluon's helicity: an event has 12 versions of
+// each, a lane forms four and reads the others from LDS (20 KB a wave, with the
+// M of the lane).  Bound: FP64 VALU at one wave per SIMD, 2.7e3 instructions a
+// wave, busy 62 % of the time; 2^20 events in 945 us (each lane all of its U and
+// W, 3.7e3 instructions: 1023 us; two waves per SIMD of 256 registers: 570 bytes
+// of scratch a lane, 1305 us).
 template <class P>
 __global__ void __launch_bounds__(64)
     sigmakin_gluon_lanes_kernel(const double* __restrict__ mom, int64_t nevt,
@@ -1176,8 +1203,7 @@ __global__ void __launch_bounds__(64)
   const int64_t i = j >> 3;
   if (i >= nevt) return;
   const int g = (int)j & 7;
-  __shared__ d2 lds[6 * 256];
-  d2* park = lds + threadIdx.x;
+  __shared__ d2 lds[GGTTG<true, ColourSum<P>>::LDS];
   double p[P::NPAR][4];
   load_event<P>(mom, i, p);
   double acc = 0.0;
@@ -1187,12 +1213,12 @@ __global__ void __launch_bounds__(64)
     if (mehel) mehel[(int64_t)h * nevt + i] = v;
     acc += (hel_mask >> h) & 1 ? v : 0.0;
   };
-  const int l0 = g & 4 ? 1 : -1, l1 = g & 2 ? 1 : -1, l2 = g & 1 ? 1 : -1;
+  const int l0 = g >> 2, l1 = (g >> 1) & 1, l2 = g & 1, ev = threadIdx.x >> 3;
   if (__all(beams_on_axis(p))) {
     set_beams(p);
-    GGTTG<true, ColourSum<P>>(p, c).flows_sum(l0, l1, l2, park, take);
+    GGTTG<true, ColourSum<P>>(p, c).flows_sum(l0, l1, l2, lds, ev, threadIdx.x, take);
   } else {
-    GGTTG<false, ColourSum<P>>(p, c).flows_sum(l0, l1, l2, park, take);
+    GGTTG<false, ColourSum<P>>(p, c).flows_sum(l0, l1, l2, lds, ev, threadIdx.x, take);
   }
   acc += dpp_move<0xB1>(acc);   // quad_perm 1 0 3 2
   acc += dpp_move<0x4E>(acc);   // quad_perm 2 3 0 1

@@ -1093,7 +1093,7 @@ HPL_PROCESSES = ('ggttgg',)
 # FP64 shares the currents between helicities instead (shared_currents.h) and
 # wins at every size, except for g g -> t t~ g below GROUP_MAX_EVENTS_F64: the
 # group kernel takes 7.2 us up to 2048 events (one wave per SIMD) and 12.6 us
-# above, the shared one 8.1 us there and 8.3 us at 4096 events.
+# above, the shared one 7.5 us there and 7.6 us at 3000 events.
 GROUP_MAX_EVENTS_F64 = {'ggttg': 2049}
 GROUP_MAX_EVENTS = {'eemumu': 1 << 16, 'ggtt': 1 << 16, 'ggttg': 1 << 16}
 # Processes whose event-per-lane kernels re-read the momenta for every
