@@ -1091,10 +1091,12 @@ HPL_PROCESSES = ('ggttgg',)
 # g g -> t t~ 4.0x at 4096, 1.55x at 2^15, 0.96x at 2^16; g g -> t t~ g 8.0x
 # at 4096, 1.36x at 2^15, 0.77x at 2^16)
 # FP64 shares the currents between helicities instead (shared_currents.h) and
-# wins at every size, except for g g -> t t~ g below GROUP_MAX_EVENTS_F64: the
-# group kernel takes 7.2 us up to 2048 events (one wave per SIMD) and 12.6 us
-# above, the shared one 7.5 us there and 7.6 us at 3000 events.
-GROUP_MAX_EVENTS_F64 = {'ggttg': 2049}
+# is faster but for launches that leave the group kernel at most two waves per
+# SIMD (beams on the axis / boosted events): g g -> t t~ up to 8192 events
+# (group 4.4 / 4.8 us to 4096 and 5.3 / 6.5 us to 8192, shared 4.5 / 7.6 us;
+# above 6.1 / 7.8 and 4.6 / 7.6 us), g g -> t t~ g up to 2048 (group 6.9 / 8.2
+# us, shared 7.2 / 8.5 us; above 12.3 / 14.9 and 7.4 / 8.7 us).
+GROUP_MAX_EVENTS_F64 = {'ggtt': 8193, 'ggttg': 2049}
 GROUP_MAX_EVENTS = {'eemumu': 1 << 16, 'ggtt': 1 << 16, 'ggttg': 1 << 16}
 # Processes whose event-per-lane kernels re-read the momenta for every
 # helicity (REREAD_MOMENTA, sigmakin_impl.h): those whose amplitude code
@@ -1161,8 +1163,13 @@ def emit_units(name):
             body = (f'  return sigmakin_gluon_lanes_launch<P_{name}>(a, mom, nevt, me, wgt, evtw, mehel,\n'
                     f'      group_max_events({GROUP_MAX_EVENTS_F64[name]}), s);\n')
         elif prec == 'f64':
-            body = (f'  return sigmakin_shared_launch<P_{name}, MG_EPL_BLOCK>(a, mom, nevt, me, wgt, evtw,\n'
-                    f'      mehel, s);\n')
+            body = ''
+            if name in GROUP_MAX_EVENTS_F64:
+                body = (f'  if (sigmakin_group_taken<P_{name}, double, MG_EPL_BLOCK>(a, a.c64, mom, nevt, me, wgt,\n'
+                        f'          evtw, mehel, group_max_events({GROUP_MAX_EVENTS_F64[name]}), s))\n'
+                        f'    return 0;\n')
+            body += (f'  return sigmakin_shared_launch<P_{name}, MG_EPL_BLOCK>(a, mom, nevt, me, wgt, evtw,\n'
+                     f'      mehel, s);\n')
         else:
             body = f'  return {epl};\n'
         src = head.format(what=f'{T} amplitudes') + '#include "sigmakin_impl.h"\n\nnamespace mg {\n' \

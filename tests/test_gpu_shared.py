@@ -69,7 +69,8 @@ def compare(eng, proc, p, prm):
     return got
 
 
-@pytest.mark.parametrize('proc,n', [(p, n) for p in PROCS for n in SIZES] + [('ggttg', 2113)])
+@pytest.mark.parametrize('proc,n', [(p, n) for p in PROCS for n in SIZES]
+                         + [('ggtt', 8257), ('ggttg', 2113)])
 def test_sizes_and_frames(mg, proc, n):
     eng = mg.MEEngine(proc, 'fp64')
     _, p, _ = orc.sample(proc, 21, 0, n)
