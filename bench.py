@@ -95,22 +95,27 @@ def recorded_traffic(proc, nevt):
     return {}
 
 
-def recorded_flops(proc, nhel):
-    """Algorithmic flops per event of proc's SIGMAKIN code from the ```flops
-    block of profiles/*.md: the executed VALU flops of the FP64 kernel of a
-    build whose amplitude code recomputes nothing
-    (`python -m paper_2106_12631_amd.build --no-recompute`), i.e. the work of
-    the amplitude code as compiled, after the products with the beams' and
-    the massless vectors' zero components have folded away.  None when no
-    record matches the current sources."""
+def recorded_flops(proc, nhel, prec):
+    """(flops per event, what they are) of proc's SIGMAKIN code in precision
+    prec from the ```flops block of profiles/*.md, None when no record matches
+    the current sources.  FP64 shares the currents between helicities: the
+    executed VALU flops of the kernel, wave instructions times 64 lanes.  The
+    other precisions: the executed flops of a build whose amplitude code
+    recomputes nothing (`python -m paper_2106_12631_amd.build --no-recompute`),
+    i.e. the work of the amplitude code as compiled, after the products with
+    the beams' and the massless vectors' zero components have folded away."""
     import glob
     import re
     want = kernel_source_hash(proc)
     for path in sorted(glob.glob(os.path.join(ROOT, 'profiles', '*.md'))):
         for blk in re.findall(r"```flops\n(.*?)```", open(path).read(), re.S):
             rec = json.loads(blk).get(proc)
-            if rec and rec.get('source_hash') == want and rec.get('nhel') == nhel:
-                return rec['flops_per_event']
+            if rec and rec.get('source_hash') == want and rec.get('nhel') == nhel and \
+                    prec in rec['flops_per_event']:
+                return rec['flops_per_event'][prec], (
+                    "measured: executed flops of the FP64 kernel, currents shared between helicities"
+                    if prec == 'fp64' else
+                    "measured: executed flops of the no-recomputation build")
     return None
 
 
@@ -480,13 +485,14 @@ def main():
                                                                     nevt, args.steps, args.warmup)
             nhel = eng.layout.nhel_good
             generic = (meta['flops_amp_per_hel'] + meta['flops_colour_per_hel']) * nhel
-            flops_evt = recorded_flops(proc, nhel)
-            source = "measured: executed flops of the no-recomputation build"
-            if flops_evt is None:
+            flops_evt, source = recorded_flops(proc, nhel, prec) or (None, "no measurement for these sources")
+            k_avg = sum(k_ms) / len(k_ms) / 1e3
+            if flops_evt is None and prec != 'fp64':
                 flops_evt = generic
                 source = "generic HELAS routine count (no measurement for these sources)"
-            k_avg = sum(k_ms) / len(k_ms) / 1e3
-            achieved = flops_evt * nevt / k_avg
+            # FP64 without a record: the routine count, helicity by helicity, is
+            # several times what the shared currents execute, and says nothing
+            achieved = flops_evt * nevt / k_avg if flops_evt else None
             peak = PEAK_FP64_VALU if prec == 'fp64' else PEAK_FP32_VALU
             v = {
                 "workload": f"{proc} {nevt} events seed {seed}",
@@ -500,9 +506,10 @@ def main():
                 "graph": {"value": graph["wall_MEs_per_s"],
                           "unit": "MEs/s (sampler + SIGMAKIN replayed from one HIP graph, wall clock)",
                           "replays_equal_eager": graph["replays_equal_eager"]},
-                "roofline": {"bound": "alu", "achieved": achieved / 1e12,
+                "roofline": {"bound": "alu", "achieved": achieved / 1e12 if achieved else None,
                              "peak": peak / 1e12, "unit": "TFLOP/s",
-                             "frac": achieved / peak, "traffic": traffic.get(prec),
+                             "frac": achieved / peak if achieved else None,
+                             "traffic": traffic.get(prec),
                              "flops_per_event": flops_evt, "flops_source": source,
                              "generic_flops_per_event": generic},
             }
@@ -513,7 +520,7 @@ def main():
                 cal = calibration['fp64_vector_fma' if prec == 'fp64'
                                   else 'fp32_vector_fma_unpacked']['achieved_TFLOPs']
                 v["roofline"]["calibrated_peak"] = cal
-                v["roofline"]["frac_vs_calibrated"] = achieved / 1e12 / cal
+                v["roofline"]["frac_vs_calibrated"] = achieved / 1e12 / cal if achieved else None
             if prec.startswith('mixed'):
                 v["mfma"] = mfma_work(meta['ncol'], nhel, prec, proc, k_avg, nevt)
             if name in cpu:

@@ -166,7 +166,8 @@ int mg_sample(const mg_handle_t* h, uint64_t seed, int64_t evt_offset, int64_t n
  * (E,0,0,E) and (E,0,0,-E), as mg_rambo writes them, take a faster body of
  * the same arithmetic with those zero components as constants (checked per
  * event where an event has a wave of its own, else for all the events of a
- * wave together); the two bodies agree to rounding. */
+ * wave together; FP64 g g -> t t~ g g has one body for both); the two bodies
+ * agree to rounding. */
 int mg_sigmakin(const mg_handle_t* h, const double* mom, int64_t nevt, double* me,
                 const double* wgt_or_null, double* evtw_or_null, void* stream);
 
@@ -191,9 +192,11 @@ int mg_sigmakin_hel(const mg_handle_t* h, const double* mom, int64_t nevt, doubl
  * by the implicit-function theorem) comes from one dual-number pass per
  * uniform.  FP64 for MG_FP64, FP32 amplitudes and adjoints with FP64 RAMBO,
  * momentum adjoints and sums otherwise.  FP64 g g -> t t~ and g g -> t t~ g
- * use the events' slots of grad_rnd as scratch (three kernels; grad_rnd may
- * still be rnd itself, at the cost of a slower kernel).  Built for e+e- -> mu+mu-, g g -> t t~ and
- * g g -> t t~ g; MG_ENOTSUP for g g -> t t~ g g. */
+ * share the currents between helicities and take RAMBO back in reverse mode,
+ * in three kernels that use the events' slots of grad_rnd as scratch
+ * (grad_rnd may still be rnd itself, at the cost of a slower kernel).  Built
+ * for e+e- -> mu+mu-, g g -> t t~ and g g -> t t~ g; MG_ENOTSUP for
+ * g g -> t t~ g g. */
 int mg_adjoint(const mg_handle_t* h, const double* rnd, int64_t nevt, const double* gbar_or_null,
                double* grad_rnd, double* grad_logw_or_null, double* f_or_null, void* stream);
 

@@ -12,6 +12,10 @@
 //   df/dr_j = (1/IDEN) (w sum_{leg,mu} d|M|^2/dp dp/dr_j + |M|^2 dw/dr_j).
 // The helicity sum, the momentum adjoints and /IDEN are in FP64; the
 // amplitudes and their adjoints in FP64 or FP32 (mixed).
+//
+// FP64 g g -> t t~ and g g -> t t~ g take the kernels of shared_adjoint.h and
+// rambo_grad.hip instead, and this one only where the gradient buffer overlaps
+// an input.
 #pragma once
 #include "common.h"
 #include "helas_adj.h"

@@ -44,12 +44,13 @@ __host__ __device__ inline int64_t aosoa_rnd(int64_t ievt, int irnd, int nrnd) {
 }
 
 // Incoming momenta along +z and -z with equal energies, (E,0,0,E) and
-// (E,0,0,-E), as RAMBO writes them in the partonic rest frame.  The SIGMAKIN
+// (E,0,0,-E), as RAMBO writes them in the partonic rest frame.  Most SIGMAKIN
 // kernels hold the amplitude body twice: for such events with the zero components
-// written as constants (set_beams; jamps<..., BEAM = true>), so that the
-// products with them fold away, and the general body for any other momenta.
-// The test is exact, so both bodies see the same values.  The gradient
-// kernel runs RAMBO itself and takes the beam body only.
+// written as constants (set_beams; BEAM = true), so that the products with them
+// fold away, and the general body for any other momenta.  The test is exact, so
+// both bodies see the same values.  The gradient kernels run RAMBO themselves
+// and take the beam body only; FP64 g g -> t t~ g g, bound by LDS, has the
+// general body only.
 template <int N>
 __device__ __forceinline__ bool beams_on_axis(const double (&p)[N][4]) {
   const double E = p[0][0];

@@ -1,14 +1,17 @@
-// SIGMAKIN kernels for one process (Sec. II, Sec. IV.b).  Per helicity the
-// generated straight-line code builds the colour-flow amplitudes and the
-// colour sum gives the helicity's |M|^2; the helicity sum is in FP64.
+// SIGMAKIN kernels for one process (Sec. II, Sec. IV.b).  FP64 launches run the
+// kernels of shared_currents.h, which form each current once for the helicities
+// it depends on, except the smallest ones of g g -> t t~ (g), which leave the
+// chip idle (sigmakin_group_kernel).  For the other precisions, whose results
+// keep the rounding of every helicity's own amplitudes, the generated
+// straight-line code builds a helicity's colour-flow amplitudes and the colour
+// sum gives its |M|^2; the helicity sum is in FP64.
 //   sigmakin_kernel          one event per lane, the loop over the kept
 //                            helicities inside the lane (the paper's layout);
 //   sigmakin_hpl_kernel      one event per wave, one helicity per lane (64
 //                            helicities): wave-uniform momenta in scalar
-//                            registers, helicity sum by wave reduction (FP32
-//                            amplitudes);
-//   sigmakin_ggttgg_shared_kernel  FP64, one event per wave, the currents
-//                            shared between helicities (shared_currents.h);
+//                            registers, helicity sum by wave reduction;
+//   sigmakin_group_kernel    several lanes per event, one helicity each, for
+//                            small launches;
 //   sigmakin_mixed_kernel    event per lane with the colour sum on the
 //                            matrix cores (colour_mfma.h);
 //   sigmakin_mixed_hpl_kernel  one event per wave, one helicity per lane,
