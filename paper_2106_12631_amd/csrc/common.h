@@ -43,6 +43,13 @@ __host__ __device__ inline int64_t aosoa_rnd(int64_t ievt, int irnd, int nrnd) {
   return ((ievt / NEPPR) * nrnd + irnd) * NEPPR + (ievt % NEPPR);
 }
 
+// Events of one launch of a kernel with `lanes` lanes per event: a grid holds
+// fewer than 2^32 work-items.  -DMG_LAUNCH_LOG2=n cuts launches at 2^n.
+#ifndef MG_LAUNCH_LOG2
+#define MG_LAUNCH_LOG2 31
+#endif
+constexpr int64_t launch_events(int lanes) { return ((int64_t)1 << MG_LAUNCH_LOG2) / lanes; }
+
 // Incoming momenta along +z and -z with equal energies, (E,0,0,E) and
 // (E,0,0,-E), as RAMBO writes them in the partonic rest frame.  Most SIGMAKIN
 // kernels hold the amplitude body twice: for such events with the zero components

@@ -749,12 +749,12 @@ struct GradGGTTG : GGTTG<true, ColourSum<P>> {
 // 3 NF), pages as the uniforms
 template <class P, class Event>
 __global__ void __launch_bounds__(64)
-    momentum_gradient_kernel(double* buf, int64_t nevt, double half, uint64_t mask,
+    momentum_gradient_kernel(double* buf, int64_t first, int64_t nevt, double half, uint64_t mask,
                              Couplings<double> c) {
   constexpr int NP = P::NPAR, NF = NP - 2, NR = 4 * NF, L = Event::LANES;
   __shared__ d2 lds[Event::LDS];
   const int64_t j = (int64_t)blockIdx.x * 64 + threadIdx.x;
-  const int64_t i = j / L;
+  const int64_t i = first + j / L;
   if (i >= nevt) return;
   const int g = (int)(j % L);
   double p[NP][4];
@@ -805,8 +805,11 @@ int shared_gradient_launch(const MeArgs& a, const RamboArgs& ra, const double* r
   constexpr int NF = P::NPAR - 2;
   const int64_t per = 64 / Event::LANES;
   launch_grad_momenta(NF, rnd, nevt, ra, grad_rnd, s);
-  momentum_gradient_kernel<P, Event><<<(unsigned)((nevt + per - 1) / per), 64, 0, s>>>(
-      grad_rnd, nevt, 0.5 * ra.sqrts, helicity_mask(a.hel), a.c64);
+  for (int64_t i = 0; i < nevt; i += launch_events(Event::LANES)) {
+    const int64_t n = std::min(nevt - i, launch_events(Event::LANES));
+    momentum_gradient_kernel<P, Event><<<(unsigned)((n + per - 1) / per), 64, 0, s>>>(
+        grad_rnd, i, nevt, 0.5 * ra.sqrts, helicity_mask(a.hel), a.c64);
+  }
   launch_grad_uniforms(NF, rnd, nevt, ra, a.inv_iden, gbar, grad_rnd, grad_logw, f, s);
   return 0;
 }

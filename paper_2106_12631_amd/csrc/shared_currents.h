@@ -24,6 +24,8 @@
 // which f V-slash acts as V-slash on a column, so that both ends of the line
 // run through the same code.
 #pragma once
+#include <algorithm>
+
 #include "common.h"
 #include "internal.h"
 
@@ -698,12 +700,12 @@ __device__ __forceinline__ double hel_value(const double* __restrict__ mom, int6
 // hel_mask: the helicities summed; mehel (or null): each helicity's value.
 template <class P>
 __global__ void __launch_bounds__(64, 2)
-    sigmakin_ggttgg_shared_kernel(const double* __restrict__ mom, int64_t nevt,
+    sigmakin_ggttgg_shared_kernel(const double* __restrict__ mom, int64_t first, int64_t nevt,
                                   double* __restrict__ me, const double* __restrict__ wgt,
                                   double* __restrict__ evtw, double* __restrict__ mehel,
                                   uint64_t hel_mask, Couplings<double> c, double inv_iden) {
   __shared__ d2 lds[ggttgg_shared::LDS_UNITS];
-  const int64_t i = xcd_event(blockIdx.x, nevt);
+  const int64_t i = first + xcd_event(blockIdx.x, gridDim.x);
   const int lane = threadIdx.x;
   double v = ggttgg_shared::hel_value<P>(mom, i, c, lds, lane);
   if (mehel) mehel[(int64_t)lane * nevt + i] = v;
@@ -724,9 +726,8 @@ __global__ void __launch_bounds__(64, 2)
 // (340 us; 75 us at one wave per SIMD, without the 36 bytes of scratch that
 // two cost).  For g g -> t t~ g that body is 1.6e5 bytes of code and spills
 // (2^20 events 1.46 ms); eight lanes per event, one for each helicity of the
-// gluons, repeat the work that one gluon's helicity would not change but need
-// no loop: 1.02 ms (2.15 ms with one amplitude per helicity).  Bound there:
-// FP64 VALU at one wave per SIMD, busy 70 % of the time.
+// gluons, take 0.95 ms (2.15 ms with one amplitude per helicity; see
+// sigmakin_gluon_lanes_kernel).
 //
 // One object per event holds what no helicity changes (momenta along the
 // quark line, propagators, the spinors of both quark helicities); flows_sum
@@ -1195,12 +1196,12 @@ __device__ __forceinline__ void ggtt_shared(const double (&p)[4][4], const Coupl
 // of scratch a lane, 1305 us).
 template <class P>
 __global__ void __launch_bounds__(64)
-    sigmakin_gluon_lanes_kernel(const double* __restrict__ mom, int64_t nevt,
+    sigmakin_gluon_lanes_kernel(const double* __restrict__ mom, int64_t first, int64_t nevt,
                                 double* __restrict__ me, const double* __restrict__ wgt,
                                 double* __restrict__ evtw, double* __restrict__ mehel,
                                 uint64_t hel_mask, Couplings<double> c, double inv_iden) {
   const int64_t j = (int64_t)blockIdx.x * 64 + threadIdx.x;
-  const int64_t i = j >> 3;
+  const int64_t i = first + (j >> 3);
   if (i >= nevt) return;
   const int g = (int)j & 7;
   __shared__ d2 lds[GGTTG<true, ColourSum<P>>::LDS];
@@ -1248,8 +1249,11 @@ int sigmakin_shared_launch(const MeArgs& a, const double* mom, int64_t nevt, dou
 template <class P>
 int sigmakin_ggttgg_shared_launch(const MeArgs& a, const double* mom, int64_t nevt, double* me,
                                   const double* wgt, double* evtw, double* mehel, hipStream_t s) {
-  sigmakin_ggttgg_shared_kernel<P><<<(unsigned)nevt, 64, 0, s>>>(mom, nevt, me, wgt, evtw, mehel,
-                                                                helicity_mask(a.hel), a.c64, a.inv_iden);
+  for (int64_t i = 0; i < nevt; i += launch_events(64)) {
+    const unsigned g = (unsigned)std::min(nevt - i, launch_events(64));
+    sigmakin_ggttgg_shared_kernel<P><<<g, 64, 0, s>>>(mom, i, nevt, me, wgt, evtw, mehel,
+                                                      helicity_mask(a.hel), a.c64, a.inv_iden);
+  }
   return 0;
 }
 

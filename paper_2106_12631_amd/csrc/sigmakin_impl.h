@@ -275,9 +275,11 @@ int sigmakin_gluon_lanes_launch(const MeArgs& a, const double* mom, int64_t nevt
   if (sigmakin_group_taken<P, double, MG_EPL_BLOCK>(a, a.c64, mom, nevt, me, wgt, evtw, mehel,
                                                     max_group, s))
     return 0;
-  const unsigned g = (unsigned)((nevt + 7) / 8);
-  sigmakin_gluon_lanes_kernel<P><<<g, 64, 0, s>>>(mom, nevt, me, wgt, evtw, mehel,
-                                                  helicity_mask(a.hel), a.c64, a.inv_iden);
+  for (int64_t i = 0; i < nevt; i += launch_events(8)) {
+    const unsigned g = (unsigned)((std::min(nevt - i, launch_events(8)) + 7) / 8);
+    sigmakin_gluon_lanes_kernel<P><<<g, 64, 0, s>>>(mom, i, nevt, me, wgt, evtw, mehel,
+                                                    helicity_mask(a.hel), a.c64, a.inv_iden);
+  }
   return 0;
 }
 
