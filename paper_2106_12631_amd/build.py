@@ -32,15 +32,6 @@ FLAGS = [
     '-I', CSRC, '-I', INCLUDE,
 ]
 
-# Flags of single sources.  The helicity-per-lane mixed kernel runs its
-# matrix-core colour sum after the FP32 amplitudes; with the MFMA results in
-# VGPRs and no VGPR spills to AGPRs it needs no AGPRs and keeps two waves per
-# SIMD.
-SOURCE_FLAGS = {
-    'sigmakin_ggttgg_mixed.hip': ['-mllvm', '-amdgpu-mfma-vgpr-form',
-                                  '-mllvm', '-amdgpu-spill-vgpr-to-agpr=0'],
-}
-
 # Flags of the generated per-process units.  Products with components that
 # are zero at compile time (the time component of a massless external
 # vector, the transverse components of the beams in the beam bodies) fold
@@ -49,6 +40,20 @@ SOURCE_FLAGS = {
 # no value for being finite: the kernels that do (count_nonfinite_kernel,
 # the cross-section and unweighting kernels) are built without the flags.
 GENERATED_FLAGS = ['-fno-signed-zeros', '-ffinite-math-only']
+
+# Flags of single sources.  The helicity-per-lane mixed kernel runs its
+# matrix-core colour sum after the FP32 amplitudes; with the MFMA results in
+# VGPRs and no VGPR spills to AGPRs it needs no AGPRs and keeps two waves per
+# SIMD.  rambo_grad.hip runs RAMBO for the gradient of g g -> t t~ (g), which
+# the generated gradient units run themselves where the gradient overwrites an
+# input: the same flags, since without them sincos, the boost and the Newton
+# step contract to other multiply-adds, and the last bits of the momenta move
+# f by up to 1.5e-9 (ill-conditioned events of a sample of 2^18).
+SOURCE_FLAGS = {
+    'sigmakin_ggttgg_mixed.hip': ['-mllvm', '-amdgpu-mfma-vgpr-form',
+                                  '-mllvm', '-amdgpu-spill-vgpr-to-agpr=0'],
+    'rambo_grad.hip': GENERATED_FLAGS,
+}
 
 
 def source_flags(src):
