@@ -182,14 +182,16 @@ struct QuarkAdjoint {
     y += up ? c1b.i : c0b.i;
   }
 
-  // to the momentum
+  // to the momentum; along -z and at rest the states are constants and P has
+  // no derivative (helicity_states, helicity_chi)
   __device__ __forceinline__ void finish(const double (&p)[4], double m, double (&pb)[4]) const {
     double vc, vx, vy, vbig, vsmall;
     helicity_states<0>(p, m, vc, vx, vy, vbig, vsmall);
     const double pt2 = p[1] * p[1] + p[2] * p[2], P2 = pt2 + p[3] * p[3];
-    const double iP = rsqrt_refined(P2), P = P2 * iP;
+    const double iP = P2 > 0.0 ? rsqrt_refined(P2) : 0.0, P = P2 * iP;
     const double ppz = p[3] >= 0.0 ? P + p[3] : pt2 * recip(P - p[3]);
-    const double nrm = rsqrt_refined(2.0 * P * ppz);  // (c, x, y) = nrm (P + pz, px, py)
+    // (c, x, y) = nrm (P + pz, px, py)
+    const double nrm = ppz > 0.0 ? rsqrt_refined(2.0 * P * ppz) : 0.0;
     const double nb = c * ppz + x * p[1] + y * p[2];
     const double Nb = -0.5 * nrm * nrm * nrm * nb;    // N = 2 P (P + pz) = nrm^-2
     const double ppzb = c * nrm + 2.0 * P * Nb;
