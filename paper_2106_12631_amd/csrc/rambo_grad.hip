@@ -200,11 +200,22 @@ __global__ void __launch_bounds__(256)
       lxi += 1.0 - b2 + q * b2;
       lb[l] = (1.0 - b2) / e[l] - q * (2.0 - b2) / e[l];
     }
+    double emean = 0.0, lmean = 0.0;
 #pragma unroll
     for (int l = 0; l < NF; ++l) {
       const double g = e[l] * ik0[l] * iden2;
       eb[l] = -xi * g * xib;
       lb[l] -= g * lxi;
+      emean += eb[l] * (1.0 / NF);
+      lmean += lb[l] * (1.0 / NF);
+    }
+    // the energies sum to sqrt(s) whatever the uniforms: what their adjoints
+    // have in common drops out, here rather than by cancellation in the sweep
+    // (all of it for two equal masses, whose weight is a constant)
+#pragma unroll
+    for (int l = 0; l < NF; ++l) {
+      eb[l] -= emean;
+      lb[l] -= lmean;
     }
   } else {
 #pragma unroll

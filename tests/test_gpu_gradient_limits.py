@@ -29,3 +29,16 @@ def test_tops_along_the_beam(mt):
     assert mg.lib().mg_adjoint(e._h, ptr(same), 2, None, ptr(same), None, ptr(f_same), stream) == 0
     assert torch.isfinite(e.rnd_events(same, 2)).all()
     assert ((f - f_same).abs() <= 1e-12 * f_same).all()
+
+
+@pytest.mark.parametrize('sqrts', [1500.0, 347.0])
+def test_two_body_weight_is_constant(sqrts):
+    """The weight of two equal masses does not depend on the uniforms: its
+    gradient is zero, with no rounding left over however soft the uniforms."""
+    import paper_2106_12631_amd as mg
+    e = mg.MEEngine('ggtt', 'fp64', params=dict(sqrts=sqrts))
+    n = (1 << 18) + 1
+    for seed in (3, 4):
+        print('[gpu-test] two-body weight', sqrts, seed, flush=True)
+        _, glogw, _ = e.adjoint(e.rng(seed, n), n)
+        assert (e.rnd_events(glogw, n) == 0.0).all()
