@@ -165,7 +165,7 @@ __global__ void __launch_bounds__(256)
     for (int m = 0; m < 3; ++m) kb[l][m] = grad[aosoa_rnd(i, 3 * l + m, NR)];
   me = grad[aosoa_rnd(i, 3 * NF, NR)];
   const Massless<NF> s(r, a.sqrts);
-  double e[NF], w = a.w0, Pb[NF][3], eb[NF], zero[NF][3], lb[NF];
+  double e[NF], w = a.w0, Pb[NF][3], eb[NF], zero[NF][3], lb[NF] = {};
 #pragma unroll
   for (int l = 0; l < NF; ++l) e[l] = s.x * s.E[l];
   bool ok = true;
@@ -221,7 +221,6 @@ __global__ void __launch_bounds__(256)
 #pragma unroll
     for (int l = 0; l < NF; ++l) {
       eb[l] = 0.0;
-      lb[l] = 0.0;
 #pragma unroll
       for (int m = 0; m < 3; ++m) Pb[l][m] = kb[l][m];
     }
@@ -233,7 +232,12 @@ __global__ void __launch_bounds__(256)
   for (int l = 0; l < NF; ++l)
 #pragma unroll
     for (int m = 0; m < 3; ++m) zero[l][m] = 0.0;
-  s.reverse(r, zero, lb, lw);
+  if (a.massive) {
+    s.reverse(r, zero, lb, lw);
+  } else {  // the weight of massless particles is a constant, collinear or not
+#pragma unroll
+    for (int k = 0; k < NR; ++k) lw[k] = 0.0;
+  }
   const double g = gbar ? gbar[i] : 1.0;
 #pragma unroll
   for (int k = 0; k < NR; ++k) {

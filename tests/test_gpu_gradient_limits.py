@@ -42,3 +42,18 @@ def test_two_body_weight_is_constant(sqrts):
         print('[gpu-test] two-body weight', sqrts, seed, flush=True)
         _, glogw, _ = e.adjoint(e.rng(seed, n), n)
         assert (e.rnd_events(glogw, n) == 0.0).all()
+
+
+@pytest.mark.parametrize('proc', ['ggtt', 'ggttg'])
+def test_massless_weight_is_constant(proc):
+    """The weight of massless particles is a constant too, also at uniforms that
+    make all of them collinear, where the momenta themselves are not defined."""
+    import paper_2106_12631_amd as mg
+    e = mg.MEEngine(proc, 'fp64', params=dict(mt=0.0, wt=0.0))
+    nr = e.layout.nrnd
+    r = torch.rand(70, nr, generator=torch.Generator().manual_seed(1), dtype=torch.float64)
+    r[::7] = 0.5
+    print('[gpu-test] massless weight', proc, flush=True)
+    grad, glogw, f = e.adjoint(e.events_rnd(r), 70)
+    assert (e.rnd_events(glogw, 70) == 0.0).all()
+    assert torch.isfinite(f.cpu()[1:7]).all() and torch.isnan(f.cpu()[::7]).all()
