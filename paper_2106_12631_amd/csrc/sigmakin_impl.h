@@ -178,11 +178,12 @@ int sigmakin_launch(const MeArgs& a, const Couplings<T>& c, const double* mom, i
 // helicity sum is a wave reduction.  The grid has exactly nevt blocks.
 template <class P, typename T>
 __global__ void __launch_bounds__(64)
-    sigmakin_hpl_kernel(const double* __restrict__ mom, int64_t nevt, double* __restrict__ me,
-                        const double* __restrict__ wgt, double* __restrict__ evtw,
-                        double* __restrict__ mehel, Couplings<T> c, double inv_iden) {
+    sigmakin_hpl_kernel(const double* __restrict__ mom, int64_t first, int64_t nevt,
+                        double* __restrict__ me, const double* __restrict__ wgt,
+                        double* __restrict__ evtw, double* __restrict__ mehel, Couplings<T> c,
+                        double inv_iden) {
   static_assert((1 << P::NPAR) == 64, "one helicity per lane of a wave64");
-  const int64_t i = xcd_event(blockIdx.x, nevt);
+  const int64_t i = first + xcd_event(blockIdx.x, gridDim.x);
   const unsigned h = threadIdx.x;
   double q[P::NPAR][4];
   load_event<P>(mom, i, q);
@@ -308,11 +309,11 @@ __device__ __forceinline__ float colour_sum_mfma_lds(const lds_float* jl,
 // 64 events), whose per-lane results are summed over the wave in FP64.
 template <class P, template <int> class CS>
 __global__ void __launch_bounds__(64)
-    sigmakin_mixed_hpl_kernel(const double* __restrict__ mom, int64_t nevt,
+    sigmakin_mixed_hpl_kernel(const double* __restrict__ mom, int64_t first,
                               double* __restrict__ me, const double* __restrict__ wgt,
                               double* __restrict__ evtw, Couplings<float> c, double inv_iden) {
   static_assert((1 << P::NPAR) == 64, "one helicity per lane of a wave64");
-  const int64_t i = xcd_event(blockIdx.x, nevt);
+  const int64_t i = first + xcd_event(blockIdx.x, gridDim.x);
   const int lane = threadIdx.x;
   double q[P::NPAR][4];
   load_event<P>(mom, i, q);
@@ -459,9 +460,11 @@ int sigmakin_guard_launch(const MeArgs& a, const double* mom, int64_t nevt, doub
 template <class P, class PH, template <int> class CS>
 int sigmakin_mixed_hpl_launch(const MeArgs& a, const double* mom, int64_t nevt, double* me,
                               const double* wgt, double* evtw, hipStream_t s) {
-  if (a.hel.n == (1 << P::NPAR) && nevt > 0 && nevt <= 0x7FFFFFFF) {
-    sigmakin_mixed_hpl_kernel<PH, CS><<<(unsigned)nevt, 64, 0, s>>>(mom, nevt, me, wgt, evtw,
-                                                                   a.c32, a.inv_iden);
+  if (a.hel.n == (1 << P::NPAR)) {
+    for (int64_t i = 0; i < nevt; i += launch_events(64)) {
+      const unsigned g = (unsigned)std::min(nevt - i, launch_events(64));
+      sigmakin_mixed_hpl_kernel<PH, CS><<<g, 64, 0, s>>>(mom, i, me, wgt, evtw, a.c32, a.inv_iden);
+    }
     return 0;
   }
   return sigmakin_mixed_launch<P, CS>(a, mom, nevt, me, wgt, evtw, s);
@@ -473,9 +476,12 @@ template <class P, typename T, int BS>
 int sigmakin_hpl_launch(const MeArgs& a, const Couplings<T>& c, const double* mom, int64_t nevt,
                         double* me, const double* wgt, double* evtw, double* mehel,
                         hipStream_t s) {
-  if ((mehel || a.hel.n == (1 << P::NPAR)) && nevt > 0 && nevt <= 0x7FFFFFFF) {
-    sigmakin_hpl_kernel<P, T><<<(unsigned)nevt, 64, 0, s>>>(mom, nevt, me, wgt, evtw, mehel, c,
-                                                           a.inv_iden);
+  if (mehel || a.hel.n == (1 << P::NPAR)) {
+    for (int64_t i = 0; i < nevt; i += launch_events(64)) {
+      const unsigned g = (unsigned)std::min(nevt - i, launch_events(64));
+      sigmakin_hpl_kernel<P, T><<<g, 64, 0, s>>>(mom, i, nevt, me, wgt, evtw, mehel, c,
+                                                a.inv_iden);
+    }
     return 0;
   }
   return sigmakin_launch<P, T, BS>(a, c, mom, nevt, me, wgt, evtw, mehel, s);
