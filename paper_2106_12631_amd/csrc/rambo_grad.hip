@@ -5,8 +5,9 @@
 // Reverse mode: with L a function of the final-state three-momenta, one sweep
 // back through the rescaling, the boost and the uniforms gives all 4 NF
 // derivatives (a second one those of log w), where a forward-mode pass is
-// needed per uniform: 2^18 g g -> t t~ g events in 45 us for both kernels.  The massless |p_i| equals its energy e_i, and the
-// rescaling xi follows the implicit-function theorem, as in rambo.h.
+// needed per uniform: 2^18 g g -> t t~ g events in 43 us for both kernels.  The
+// massless |p_i| equals its energy e_i, and the rescaling xi follows the
+// implicit-function theorem, as in rambo.h.
 #include "common.h"
 #include "internal.h"
 #include "rambo.h"

@@ -170,8 +170,11 @@ __device__ __forceinline__ double rsqrt_refined(double x) {
 }
 
 // sqrt(x) from y = rsqrt_refined(x), x > 0: x y corrected by its residual, so
-// that it rounds as the square root does (x y alone is off by up to 1.5 ulp;
-// rms error of 2^24 matrix elements of e+ e- -> mu+ mu- 5.9e-16, so 5.6e-16)
+// that it rounds as the square root does (x y alone is off by up to 1.5 ulp).
+// rms error of 65536 matrix elements of e+ e- -> mu+ mu- at 1500 GeV against 80
+// bits 3.5e-16, and 4.0e-16 with one amplitude per helicity (against 64 bits 5.7e-16
+// and 5.5e-16: most of that is the rounding of the 64-bit evaluation, which
+// rounds like the latter)
 __device__ __forceinline__ double sqrt_refined(double x, double y) {
   const double s = x * y;
   return fmadd(0.5 * y, fmadd(-s, s, x), s);
